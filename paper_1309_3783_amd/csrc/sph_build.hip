@@ -269,7 +269,7 @@ __global__ void k_top_cells(const SetInfo* sets, int nsets, int ntop, int bmax,
 // One wave per cell of level `level`: particle range (children of a split
 // parent look theirs up inside the parent's range), max decision h, the
 // number with h < edge/2, and the split decision.
-__global__ __launch_bounds__(256) void k_cell_stats(const SetInfo* sets, int bmax, int level,
+__global__ __launch_bounds__(256) void k_cell_stats(SetInfo* sets, int bmax, int level,
                                                     int64_t c0, int64_t c1, const uint64_t* __restrict__ key,
                                                     const float* __restrict__ hdec, int n_split,
                                                     float split_frac, Cell* __restrict__ cells) {
@@ -303,6 +303,8 @@ __global__ __launch_bounds__(256) void k_cell_stats(const SetInfo* sets, int bma
         C.split = (level < S.depth && C.count > n_split &&
                    (double)nsmall > (double)split_frac * (double)C.count) ? 1u : 0u;
         cells[c] = C;
+        // (every writer writes the same value)
+        if (C.split || (level == 0 && C.count >= SCAN_MIN)) sets[C.set].uneven = 1;
     }
 }
 
@@ -615,7 +617,8 @@ __global__ __launch_bounds__(256) void k_chunk_cost(const int4* __restrict__ chu
                                                     const Cell* __restrict__ cells, const SetInfo* __restrict__ sets,
                                                     const uint32_t* __restrict__ csr_off,
                                                     const uint64_t* __restrict__ csr, float piece,
-                                                    uint32_t* __restrict__ pcount, uint32_t* __restrict__ poff,
+                                                    float* __restrict__ pcost, uint32_t* __restrict__ pcount,
+                                                    uint32_t* __restrict__ poff,
                                                     uint32_t* __restrict__ total) {
     const int lane = threadIdx.x & 63;
     const int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -668,9 +671,73 @@ __global__ __launch_bounds__(256) void k_chunk_cost(const int4* __restrict__ chu
     int pn = 0;
     if (piece > 0.f && est >= piece) pn = min((int)ceilf(8.f * est / piece), PIECE_MAX);
     pcount[c] = (uint32_t)pn;
+    if (pcost) pcost[c] = est;
     if (pn > 0) {
         poff[c] = atomicAdd(&total[0], (uint32_t)pn);
         atomicAdd(&total[1], 1u);
+    }
+}
+
+// The order in which each work range's chunks are handed out: those of the
+// longest estimated walks first, so that the waves end at about the same
+// time, in ORDER_CLASSES classes by factors of two, each in cell order
+// (neighbours in space share partner data).  One block per range; the first
+// also counts the sets that are not uneven.
+constexpr int ORDER_CLASSES = 4;
+constexpr float ORDER_LONG = 8192.f;
+__global__ __launch_bounds__(1024) void k_chunk_order(const uint32_t* __restrict__ nch_dev,
+                                                      const float* __restrict__ pcost, uint32_t* __restrict__ order,
+                                                      const SetInfo* __restrict__ sets, int nsets,
+                                                      uint32_t* __restrict__ nplain) {
+    const int64_t nch = (int64_t)*nch_dev;
+    const int64_t lo = nch * blockIdx.x / gridDim.x, hi = nch * (blockIdx.x + 1) / gridDim.x;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    __shared__ uint32_t s_n[ORDER_CLASSES];          // first the counts, then the next places
+    __shared__ uint32_t s_w[16][ORDER_CLASSES];
+    if (blockIdx.x == 0)
+        for (int s = threadIdx.x; s < nsets; s += 1024)
+            if (sets[s].count > 0 && !sets[s].uneven) atomicAdd(nplain, 1u);
+    if (!order) return;
+    if (threadIdx.x < ORDER_CLASSES) s_n[threadIdx.x] = 0;
+    __syncthreads();
+    auto cls = [](float est) {
+        int k = 0;
+        for (float t = ORDER_LONG; k < ORDER_CLASSES - 1 && est < t; t *= 0.5f) ++k;
+        return k;
+    };
+    for (int64_t c = lo + threadIdx.x; c < hi; c += 1024) atomicAdd(&s_n[cls(pcost[c])], 1u);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t at = 0;
+        for (int k = 0; k < ORDER_CLASSES; ++k) {
+            const uint32_t n = s_n[k];
+            s_n[k] = at;
+            at += n;
+        }
+    }
+    __syncthreads();
+    for (int64_t c0 = lo; c0 < hi; c0 += 1024) {
+        const int64_t c = c0 + threadIdx.x;
+        const int mine = c < hi ? cls(pcost[c]) : -1;
+        uint32_t rank = 0;
+        for (int k = 0; k < ORDER_CLASSES; ++k) {
+            const uint64_t m = __ballot(mine == k);
+            if (lane == 0) s_w[w][k] = (uint32_t)__popcll(m);
+            if (mine == k) rank = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        }
+        __syncthreads();
+        if (threadIdx.x < ORDER_CLASSES) {
+            uint32_t at = s_n[threadIdx.x];
+            for (int v = 0; v < 16; ++v) {
+                const uint32_t n = s_w[v][threadIdx.x];
+                s_w[v][threadIdx.x] = at;
+                at += n;
+            }
+            s_n[threadIdx.x] = at;
+        }
+        __syncthreads();
+        if (mine >= 0) order[lo + s_w[w][mine] + rank] = (uint32_t)c;
+        __syncthreads();
     }
 }
 
@@ -1426,6 +1493,7 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
         sets[s].count = in->offsets[s + 1] - in->offsets[s];
         sets[s].box = in->box[s];
         sets[s].drift = 0.f;
+        sets[s].uneven = 0;
     }
     HIPTRY(hipMemcpyAsync(d_sets, sets.data(), sizeof(SetInfo) * S, hipMemcpyHostToDevice, st));
     std::vector<float> hmax(S, 0.f), hmin(S, INFINITY);
@@ -1734,25 +1802,40 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
     const bool pieces = piece_rec > 0 && chunk_cap < ((int64_t)1 << 27);
     ERRTRY(t->alloc(t->b_piece, 2 * sizeof(uint32_t) * chunk_cap, (void**)&t->pcount));
     t->poff = t->pcount + chunk_cap;
-    HIPTRY(fill_u32(total + 18, 2, 0u, st));
+    // (the estimates, and the order made from them)
+    const bool cost_now = t->nlevels > 1 && t->n > 0;
+    t->pcost = nullptr;
+    t->order = nullptr;
+    if (cost_now && t->try_alloc(t->b_order, 2 * sizeof(uint32_t) * chunk_cap, (void**)&t->pcost))
+        t->order = (uint32_t*)(t->pcost + chunk_cap);
+    HIPTRY(fill_u32(total + 18, 3, 0u, st));
     auto chunk_cost = [&]() -> Err {
         hipLaunchKernelGGL(k_chunk_cost, dim3(nblk(chunk_cap, 4)), dim3(256), 0, st, t->chunks, total, chunk_cap,
-                           t->cells, d_sets, t->csr_off, t->csr, (float)piece_rec, t->pcount, t->poff, total + 18);
+                           t->cells, d_sets, t->csr_off, t->csr, pieces ? (float)piece_rec : 0.f, t->pcost, t->pcount,
+                           t->poff, total + 18);
         HIPTRY(hipGetLastError());
         return Err{};
     };
-    const bool cost_now = pieces && t->nlevels > 1;
-    if (cost_now) ERRTRY(chunk_cost());
-    else HIPTRY(fill_u32(t->pcount, chunk_cap, 0u, st));
+    if (cost_now) {
+        ERRTRY(chunk_cost());
+        hipLaunchKernelGGL(k_chunk_order, dim3(NGRP), dim3(1024), 0, st, total, t->pcost, t->order, d_sets, t->nsets,
+                           total + 20);
+        HIPTRY(hipGetLastError());
+    } else {
+        HIPTRY(fill_u32(t->pcount, chunk_cap, 0u, st));
+    }
     // chunk count (total[0], untouched since its scan), leaves, largest
-    // leaf, pieces, heavy chunks
+    // leaf, pieces, heavy chunks, sets that are not uneven
     static_assert(sizeof(int) == sizeof(uint32_t), "layout of the count words");
-    ERRTRY(read_back(ctx, total, 20 * sizeof(uint32_t), &rb));
+    ERRTRY(read_back(ctx, total, 21 * sizeof(uint32_t), &rb));
     const uint32_t nchunks = ((const uint32_t*)rb)[0];
     t->nleaves = ((const int*)rb)[16];
     t->max_leaf = ((const int*)rb)[17];
     t->npieces = ((const uint32_t*)rb)[18];
     t->nheavy = ((const uint32_t*)rb)[19];
+    // (a tree of one level whose top cells are large is taken to have some,
+    // unless it is of one set: that set is uneven then)
+    t->nplain = cost_now ? ((const uint32_t*)rb)[20] : t->nsets - 1;
     t->nchunks = nchunks;
     if ((int64_t)nchunks > chunk_cap) return Err{SPH_E_STATE, "internal: chunk count above its bound"};
     if (pieces && !cost_now && 27 * t->max_leaf >= piece_rec) {

@@ -30,10 +30,12 @@ struct sph_ctx {
     // device words (CTR_WORDS): [0, 256) density work counters, [256, 512)
     // force work counters, [512, 768) chunk-list counts, [CTR_CFL] Courant
     // minimum, [CTR_WORK, +512): 64-bit counts of pair evaluations, density
-    // then force, each spread over 8 counters 128 bytes apart
+    // then force, each spread over 8 counters 128 bytes apart, [CTR_PARK] and
+    // 128 bytes on: walks parked in a density / force pass
     int32_t* d_counter = nullptr;
     static constexpr int CTR_CFL = 768;
     static constexpr int CTR_WORK = 1024;
+    static constexpr int CTR_PARK = 1600;
     static constexpr int CTR_WORDS = 2048;
     // pinned host memory that device counts are read back into: one
     // asynchronous copy per read, then one stream synchronisation
@@ -139,7 +141,8 @@ struct sph_tree {
     sph::DevBuf b_sets, b_small, b_key, b_key2, b_val, b_val2, b_perm, b_pos, b_plo, b_pv, b_ph, b_hdec, b_pu,
         b_bound, b_mix, b_rs, b_cell, b_taskA, b_taskB, b_final, b_chunk, b_csr, b_csr2, b_csroff,
         b_segoff, b_seglist, b_segproj, b_segidx, b_bigk, b_bigv, b_sc, b_dens, b_force, b_solve,
-        b_red, b_misc, b_saved, b_split, b_counts, b_iperm, b_owned, b_blk, b_piece, b_plist, b_part, b_inrec;
+        b_red, b_misc, b_saved, b_split, b_counts, b_iperm, b_owned, b_blk, b_piece, b_plist, b_part, b_inrec,
+        b_order, b_park;   // (these two optional, see try_alloc)
 
     // ---- sizes (host) --------------------------------------------------
     int64_t ncells = 0, ntasks = 0, npairs = 0, nsegent = 0, nchunks = 0, max_leaf = 0;
@@ -184,6 +187,13 @@ struct sph_tree {
     uint32_t* plist = nullptr;
     double* part = nullptr;
     int64_t npieces = 0, nheavy = 0;
+    // walks shared by a block's waves: slots for the walks that a pass parks,
+    // or every chunk from its start
+    int64_t nslots = 0;
+    bool direct = false;
+    int64_t nplain = 0;          // sets with particles that are not uneven (see SetInfo), where a tree is ext()
+    float* pcost = nullptr;      // per chunk: the records its walk is estimated to read
+    uint32_t* order = nullptr;   // each range's chunks, the longest walks first (null: in their own order)
     int32_t max_sorted = INT32_MAX;   // partners with more particles have no sorted lists (read in cell order)
     // whether the interaction kernels need the code for heavy chunks and
     // cell-order reads: the tree has heavy chunks, or some partner cell may
@@ -241,7 +251,7 @@ struct sph_tree {
                 &b_pu, &b_bound, &b_mix, &b_rs, &b_cell, &b_taskA, &b_taskB, &b_final, &b_chunk, &b_csr,
                 &b_csr2, &b_csroff, &b_segoff, &b_seglist, &b_segproj, &b_segidx, &b_bigk, &b_bigv, &b_sc,
                 &b_dens, &b_force, &b_solve, &b_red, &b_misc, &b_saved, &b_split, &b_counts, &b_iperm, &b_owned,
-                &b_blk, &b_piece, &b_plist, &b_part, &b_inrec};
+                &b_blk, &b_piece, &b_plist, &b_part, &b_inrec, &b_order, &b_park};
     }
 
     // Drop every buffer (the tree must be built again).  Library-owned
@@ -257,13 +267,26 @@ struct sph_tree {
             m->cap = 0;
         }
         if (ws) ar.reset(ar.base, ar.cap);
+        pcost = nullptr;
+        order = nullptr;
+        nslots = 0;
         built = sorted = have_density = have_ghost = false;
         saved = false;
         nsegent = 0;
     }
 
     // A new block of at least `bytes` (want: the preferred, larger size).
+    // The optional blocks (try_alloc) make room for it if they must.
     sph::Err take(size_t bytes, size_t want, void** p, size_t* got) {
+        const size_t needed = ws_needed;
+        sph::Err e = take_once(bytes, want, p, got);
+        if (e.st && drop_optional()) {
+            ws_needed = needed;
+            e = take_once(bytes, bytes, p, got);
+        }
+        return e;
+    }
+    sph::Err take_once(size_t bytes, size_t want, void** p, size_t* got) {
         if (ws) {
             size_t off;
             if (ar.take(want, &off)) {
@@ -315,6 +338,39 @@ struct sph_tree {
         }
         *out = b.p;
         return sph::Err{};
+    }
+
+    // alloc of a block that the tree can do without: false if there is no room
+    bool try_alloc(sph::DevBuf& b, size_t bytes, void** out) {
+        if (b.cap < bytes) {
+            give(b.p, b.cap);
+            b.p = nullptr;
+            b.cap = 0;
+            const size_t needed = ws_needed;
+            size_t got = 0;
+            if (take_once(bytes, bytes + bytes / 8, &b.p, &got).st) {
+                ws_needed = needed;
+                return false;
+            }
+            b.cap = got;
+        }
+        *out = b.p;
+        return true;
+    }
+    // Give the optional blocks back: what is enqueued with them runs before
+    // any use of the memory by others (see give), later launches go without.
+    bool drop_optional() {
+        bool any = false;
+        for (sph::DevBuf* b : {&b_order, &b_park}) {
+            any = any || b->p;
+            give(b->p, b->cap);
+            b->p = nullptr;
+            b->cap = 0;
+        }
+        pcost = nullptr;
+        order = nullptr;
+        nslots = 0;
+        return any;
     }
 
     // grow keeping the first `keep` bytes (copied on the stream)

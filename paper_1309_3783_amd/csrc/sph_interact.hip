@@ -39,6 +39,7 @@
 // within their bars up to ~1600 neighbours.
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "sph_impl.h"
 
@@ -48,6 +49,9 @@ constexpr float C8PI = 2.5464790894703255f;   // 8/pi: cubic-spline normalisatio
 constexpr int BLK = 256;                      // 4 wavefronts per block, each independent
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uni64(uint64_t v) {
+    return ((uint64_t)(uint32_t)uni((int)(v >> 32)) << 32) | (uint32_t)uni((int)v);
+}
 // Number of set bits of m in the lanes below this one (two mbcnt
 // instructions; no 64-bit lane mask in registers).
 __device__ __forceinline__ int bits_below(uint64_t m) {
@@ -66,14 +70,15 @@ __device__ __forceinline__ float frsq(float x) { return __builtin_amdgcn_rsqf(x)
 // the XCDs in turn), so the chunks one XCD works on at a time are neighbours
 // and share partner data in that XCD's L2; a wave whose range is exhausted
 // moves on to the following ranges.  ctr holds NGRP counters (CSTRIDE
-// words apart), zero at launch.  In a Newton pass after the first, the
+// words apart), zero at launch.  Where the build ordered them (k_chunk_order),
+// a range's chunks are handed out in the order of list, those of the longest
+// estimated walks first.  In a Newton pass after the first, the
 // ranges hold only the chunks that still have active particles: lcount[g *
 // CSTRIDE] of them, listed from the start of range g in list (made by
 // k_chunk_list), so that a pass in which few particles are left costs a
 // few atomics rather than one per chunk.  A wave looking past its own range
 // first reads the counter and skips a range already handed out, without an
 // atomic.  Which wave takes which chunk changes no result.
-constexpr int NGRP = 8;
 // the counters sit 128 bytes apart: atomics on one cache line from all XCDs
 // serialise
 constexpr int CSTRIDE = 32;
@@ -84,7 +89,7 @@ __device__ __forceinline__ int next_chunk(int* __restrict__ ctr, int nchunks, co
         const int g = (home + k) & (NGRP - 1);
         const int lo = (int)((int64_t)nchunks * g / NGRP);
         const int hi = (int)((int64_t)nchunks * (g + 1) / NGRP);
-        const int cnt = list ? uni(lcount[g * CSTRIDE]) : hi - lo;
+        const int cnt = lcount ? uni(lcount[g * CSTRIDE]) : hi - lo;
         const bool open =
             cnt > 0 && (k == 0 || __hip_atomic_load(&ctr[g * CSTRIDE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < cnt);
         if (open) {
@@ -109,17 +114,20 @@ __device__ __forceinline__ int next_chunk(int* __restrict__ ctr, int nchunks, co
 // within one range, one atomic per block.  lcount must be zero on entry; the
 // order inside a range follows the blocks' atomics and changes no result.
 // active is read as 8-byte words: its buffer is 8-byte aligned and padded
-// past the last particle.
+// past the last particle.  order: the build's order of each range's chunks
+// (null: as they are).
 constexpr int LIST_BS = 256;
 __global__ __launch_bounds__(LIST_BS) void k_chunk_list(const int4* __restrict__ chunks, int nchunks, int bpg,
-                                                        const uint8_t* __restrict__ active, uint32_t* __restrict__ list,
+                                                        const uint8_t* __restrict__ active,
+                                                        const uint32_t* __restrict__ order, uint32_t* __restrict__ list,
                                                         int* __restrict__ lcount) {
     const int g = blockIdx.x / bpg, part = blockIdx.x - g * bpg;
     const int lo = (int)((int64_t)nchunks * g / NGRP);
     const int hi = (int)((int64_t)nchunks * (g + 1) / NGRP);
-    const int c = lo + part * LIST_BS + (int)threadIdx.x;
+    int c = lo + part * LIST_BS + (int)threadIdx.x;
     bool on = false;
     if (c < hi) {
+        if (order) c = (int)order[c];   // (the blocks of a range take their places about in this order)
         const int4 ch = chunks[c];
         const int64_t a = ch.y, b = (int64_t)ch.y + ch.z;   // particles [a, b)
         const uint64_t* w = reinterpret_cast<const uint64_t*>(active);
@@ -310,6 +318,9 @@ struct DensArgs {
     const uint32_t* plist;  // the pieces (chunk << 5 | piece), handed out first
     int npieces;
     double* part;           // partial sums of the pieces of split chunks
+    char* park;             // slots of parked walks (see walk), how many there are,
+    int slots;
+    int* taken;             // how many were asked for in this pass (zero at launch)
     const int32_t* status;
     float *rho, *drho, *nw, *dnw;
     int32_t* nngb;
@@ -381,6 +392,9 @@ __device__ __forceinline__ float comb_max(float v, int R) {
 constexpr int TCAP = SPH_TCAP;
 constexpr int NWORD = TCAP / 32;
 static_assert(TCAP % 32 == 0 && TILE - TCAP >= 16, "tile layout");
+// (a block's tiles lie side by side, one per wave)
+// Slot of the s-th record of the block's tiles taken as one buffer.
+__device__ __forceinline__ int tile_slot(int s) { return s + s / TCAP * (TILE - TCAP); }
 
 // Test of a lane's share [j0, j0 + share) of the tile (share <= TCAP; the
 // tile is padded past its end): bit k of word w set when record
@@ -427,10 +441,11 @@ __device__ __forceinline__ void tile_test(const float4* sp, int j0, int share, c
     }
 }
 
-// Test and evaluation of the n (1 <= n <= TCAP) records staged in S; self:
-// the tile holds a block of the self task (wave-uniform).
-template <class P>
-__device__ __forceinline__ void process_tile(typename P::Lds& S, int n, int R, int rep, const typename P::Lane& L,
+// Test and evaluation of the n (1 <= n <= TCAP) records staged in the tile
+// at slot off of S, into the FP32 sums of acc; self: the tile holds a block
+// of the self task (wave-uniform).
+template <class P, class Lds>
+__device__ __forceinline__ void process_tile(Lds& S, int off, int n, int R, int rep, const typename P::Lane& L,
                                              typename P::Acc& acc, bool self) {
     const int lane = threadIdx.x & 63;
     // far-away padding: every share has the same length (R * share - n < 16)
@@ -439,11 +454,11 @@ __device__ __forceinline__ void process_tile(typename P::Lds& S, int n, int R, i
         // compiler would otherwise hold it in four registers or spill it)
         float far = FAR;
         asm volatile("" : "+v"(far));
-        S.p[n + lane] = make_float4(far, far, far, 0.f);
+        S.p[off + n + lane] = make_float4(far, far, far, 0.f);
     }
     wave_lds_sync();
     const int share = (n + R - 1) >> (31 - __builtin_clz(R));
-    const int j0 = rep * share;
+    const int j0 = off + rep * share;
     uint32_t m[NWORD];
     // (an idle lane sits at -FAR: no record is ever within its h)
     const float hi2 = L.h * L.h;
@@ -461,7 +476,6 @@ __device__ __forceinline__ void process_tile(typename P::Lds& S, int n, int R, i
             P::pair(acc, S, j0 + 32 * w + k, L);
         }
     }
-    P::fold(acc);
     wave_lds_sync();   // the tile is overwritten next
 }
 
@@ -678,6 +692,69 @@ __device__ __forceinline__ int skip_blocks(const float4* __restrict__ blkbox, co
     return g0 + ((to - g0) & ~(BLK - 1));
 }
 
+// The end of a pass (EXT).  A chunk's walk may be tens of times longer than
+// the average one (a leaf next to a clump), and once no chunk is left to hand
+// out the last waves would walk on alone, at the speed of one wave's
+// dependent steps: on a clumpy set of 10^6 particles a density pass took 2.9
+// ms, 0.85 ms of which is the waves' time divided by the waves that fit.  So
+// a wave that still walks GRACE tiles after the last chunk was handed out
+// parks its walk: sums so far and place go to a slot in memory, and the next
+// kernel's blocks go on with the parked walks, eight waves each.
+// The staged sequence of records, the tiles it is cut into and the order in
+// which the tiles' sums are added are those of one wave, so that a parked
+// walk ends with bitwise the same results.  This needs every sum to be added
+// up tile by tile: force chunks of sets whose du and S run on in FP32 (sets
+// of one level, see ForceP::fold) are never parked.
+// The tiles that a walk goes on for, and those from which it is taken for a
+// long one: with fewer, walks about to end take up the slots and the time of
+// the second kernel (100 sets of 27685, 7% of the passes after the first),
+// with more, the longest go on alone for longer (a set of 10^6, density and
+// force: 5.6 ms with 24 and 48, 6.6 with 64 and 96, 9.2 without parking).
+// The counters are not read before the walk is about that long: the loads
+// from all waves cost the density passes over 8 * 10^6 particles 10%.
+constexpr int GRACE = 24;
+constexpr int PARK_MIN = 48;
+
+// Where a parked walk goes on: the group of records whose first `skip` passing
+// ones are processed (kind 1 = a block of the self task from particle at, 2 =
+// the records from sequence index at of the batch of cell A's entries from e0
+// on; 0 = the walk's start), and how many of the records staged before were
+// the self task's beyond the tiles processed.
+struct Cursor {
+    int kind, at, skip, A, nself;
+    uint32_t e0;
+};
+
+// No chunk is left in this XCD's range, nor in the one half way round (a wave
+// done with its own range goes on to the following ones).
+template <class A>
+__device__ __forceinline__ bool handed_out(const A& a) {
+    bool all = true;
+    for (int k = 0; k < NGRP; k += NGRP / 2) {
+        const int g = (blockIdx.x + k) & (NGRP - 1);
+        const int cnt = a.lcount ? uni(a.lcount[g * CSTRIDE])
+                                 : (int)((int64_t)a.nchunks * (g + 1) / NGRP) - (int)((int64_t)a.nchunks * g / NGRP);
+        all = all && __hip_atomic_load(&a.counter[g * CSTRIDE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= cnt;
+    }
+    return all;
+}
+
+// A cell's record in scalar registers (the same cell on every lane).
+__device__ __forceinline__ Cell uni_cell(const Cell& c) {
+    Cell u = c;
+    u.first = uni(c.first);
+    u.count = uni(c.count);
+    u.parent = uni(c.parent);
+    u.ix = uni(c.ix);
+    u.iy = uni(c.iy);
+    u.iz = uni(c.iz);
+    u.level = (int16_t)uni(c.level);
+    u.set = (int16_t)uni(c.set);
+    u.hcur = unif(c.hcur);
+    u.hcur_l = unif(c.hcur_l);
+    return u;
+}
+
 // The walk of one chunk, in one frame (origin oA relative to the leaf's top
 // cell; the lanes' coordinates are in that frame), or of piece k of P of a
 // split chunk (pm = k | P << 5; 1 << 5 for a whole chunk: the piece takes
@@ -689,14 +766,25 @@ __device__ __forceinline__ int skip_blocks(const float4* __restrict__ blkbox, co
 // plus the largest cutoff, or (EXT) reads a dense partner in cell order.
 // The swept records of a batch of pair tasks are staged in sequence, each
 // step filling the current tile; written as one loop so that the tile
-// processing is inlined once.  The records loaded are added to *nread (a
-// word of the wave's in LDS, by its first lane).
-template <class P, bool EXT>
-__device__ __forceinline__ void walk(const typename P::Args& a, typename P::Lds& S, SweepTab& T,
-                                    const typename P::Lane& L, typename P::Acc& acc, int leaf, const Frame& fr,
-                                    int R, int rep, bool act, int pm, unsigned long long* nread) {
+// processing is inlined once.  tiles: every sum is added up in FP64 over the
+// tiles (ForceP::fold).  The records loaded are added to *nread (a word of
+// the wave's in LDS, by its first lane).
+//
+// W = 1: one wave, S's tile from slot base on; returns true if the walk is to
+// be parked (in slot pslot; cur: where it goes on).  W > 1: the block's W waves go
+// on from cur.  Every wave follows the whole sequence of groups of 64
+// records and builds the sweep descriptors for itself, but loads and filters
+// only every W-th group; the counts of the others (mc, two sets used in
+// turn) give the places of its records in the W tiles, and once these are
+// full each wave processes one.  The first wave's acc receives the tiles'
+// sums in their order, as if it had walked alone.
+template <class P, bool EXT, int W, class Lds>
+__device__ __forceinline__ bool walk(const typename P::Args& a, Lds& S, int base, int wi, int* mc,
+                                    SweepTab& T, const typename P::Lane& L, typename P::Acc& acc, int leaf,
+                                    const Frame& fr, int R, int rep, bool act, int pm, bool tiles, bool may_park,
+                                    int& pslot, Cursor& cur, unsigned long long* nread) {
     const int lane = threadIdx.x & 63;
-    const Cell C = a.cells[leaf];
+    const Cell C = uni_cell(a.cells[leaf]);
     const int cend = C.first + C.count;
     const int pk = pm & 31, pn = pm >> 5;
     int sbase = C.first + 64 * pk;   // next record of the self task
@@ -712,23 +800,116 @@ __device__ __forceinline__ void walk(const typename P::Args& a, typename P::Lds&
     // the cell whose pair tasks are walked and its entries still to load
     int A = leaf;
     Cell cA = C;
-    float L0 = (float)a.sets[C.set].L0;
-    uint32_t e = a.csr_off[A], e1 = a.csr_off[A + 1];
+    float L0 = unif((float)a.sets[C.set].L0);
+    const float tiny = 1e-5f * L0;
+    uint32_t e = uni((int)a.csr_off[A]), e1 = uni((int)a.csr_off[A + 1]);
+    uint32_t e0 = e;                 // the first entry of the batch
     int nd = 0, tot = 0, g0 = 0;     // descriptors of the batch, their records, records loaded
     int hold = 0;                    // records before this index need no block test
-    int fill = 0;
-    bool tself = false;   // the current tile holds records of the self task
+    int fill = 0;                    // records staged
+    int nself = 0;                   // of them, records of the self task (from the first one staged)
+    int skip = 0;                    // passing records to leave out (the first group of a resumed walk)
+    int turn = 0, late = 0, seen = 0;
+    // the batch of entries from e on (a batch may sweep no records at all)
+    auto next_batch = [&]() {
+        const int n = (int)min(e1 - e, (uint32_t)DBATCH);
+        bool co_any;
+        nd = build_sweeps<P, EXT>(a, cA, L0, fr, e, n, bx, hmax, T, &tot, &co_any);
+        tot = uni(tot);
+        e0 = e;
+        e += n;
+        g0 = 0;
+        hold = co_any ? 0 : tot;   // blocks are tested in parts read in cell order only
+    };
+    if (W > 1 && cur.kind != 0) {
+        skip = uni(cur.skip);
+        nself = uni(cur.nself);
+        if (uni(cur.kind) == 1) {
+            sbase = uni(cur.at);
+        } else {
+            sbase = cend;
+            A = uni(cur.A);
+            cA = uni_cell(a.cells[A]);
+            L0 = unif((float)a.sets[cA.set].L0);
+            e = uni((int)cur.e0);
+            e1 = uni((int)a.csr_off[A + 1]);
+            next_batch();
+            g0 = uni(cur.at);
+        }
+    }
     // a record is staged only if it lies within the cutoff of the chunk's
     // bounding box (the sweep bounds the distance along the pair axis only)
     const float lox = -bx[3], loy = -bx[4], loz = -bx[5];
-    const float tiny = 1e-5f * L0;
     const float rw = 1.2f * fmaf(hmax, 1.000002f, tiny);
     const float rwide2 = rw * rw;
     const float rs = fmaf(P::cut(hmax, fmaxf(C.hcur, C.hcur_l)), 1.000002f, tiny);
     const float rself2 = rs * rs;
     for (;;) {
-        bool done = false, self = false;
-        int nuse = 0;
+        // the next group of each wave: kind 1 = a block of the self task, 2 =
+        // 64 records of the batch's sequence, 0 = none this round (a new
+        // batch waits until the groups of the last one are loaded)
+        bool done = false;
+        int kind = 0, at = 0, nuse = 0;
+        int selfw = 0;   // waves with a block of the self task
+#pragma unroll 1
+        for (int v = 0; v < W; ++v) {
+            int kk = 0, kat = 0, kn = 0;
+            if (sbase < cend) {
+                kk = 1;
+                kat = sbase;
+                kn = min(64, cend - sbase);
+                sbase += 64 * pn;   // (a piece: the next block of its own)
+                selfw |= 1 << v;
+            } else {
+                const bool fresh = selfw == (1 << v) - 1;   // no group of a batch taken this round
+                // of this cell, or of its ancestors
+                for (;;) {
+                    if (W > 1 && g0 >= tot && !fresh) break;
+                    while (g0 >= tot) {
+                        while (e >= e1 && A >= 0) {
+                            A = cA.parent;
+                            if (A >= 0) {
+                                cA = uni_cell(a.cells[A]);
+                                L0 = unif((float)a.sets[cA.set].L0);
+                                e = uni((int)a.csr_off[A]);
+                                e1 = uni((int)a.csr_off[A + 1]);
+                            }
+                        }
+                        if (A < 0) {
+                            done = v == 0;
+                            break;
+                        }
+                        next_batch();
+                    }
+                    if (g0 >= tot) break;
+                    if (EXT && W == 1 && pn > 1) {
+                        // a piece takes the groups of 64 records k, k + P, ...
+                        const int r = ((g0 >> 6) - pk) % pn;
+                        if (r != 0) g0 += 64 * (pn - (r < 0 ? r + pn : r));
+                        if (g0 >= tot) continue;
+                    }
+                    if (!EXT || !a.skip || g0 < hold) {
+                        kk = 2;
+                        break;
+                    }
+                    // pass over the blocks of a part read in cell order that lie
+                    // beyond the chunk's reach
+                    g0 = uni(skip_blocks<P>(a.blkbox, T, nd, g0, lox, loy, loz, bx, hmax, tiny, &hold));
+                    hold = uni(hold);
+                }
+                if (kk == 2) {
+                    kat = g0;
+                    kn = min(64, tot - g0);
+                    g0 += kn;
+                }
+            }
+            if (W == 1 || v == wi) {
+                kind = kk;
+                at = kat;
+                nuse = kn;
+            }
+            if (kk == 0) break;
+        }
         uint32_t j = 0;                     // the lane's record: particle, position, shift, radius^2
         float4 pj = make_float4(0.f, 0.f, 0.f, 0.f);
         float Sx = 0.f, Sy = 0.f, Sz = 0.f, rad2 = 0.f;
@@ -736,10 +917,9 @@ __device__ __forceinline__ void walk(const typename P::Args& a, typename P::Lds&
         int dl = -1;
         bool co = false;                    // a record of a part read in cell order
         typename P::Pre pre{};
-        if (sbase < cend) {
-            // a block of the self task
-            nuse = min(64, cend - sbase);
-            j = (uint32_t)(sbase + lane);
+        if (lane == 0) *nread += (unsigned long long)nuse;
+        if (kind == 1) {
+            j = (uint32_t)(at + lane);
             q = j;
             if (lane < nuse) pj = a.pos[j];
             const float3 oA = fr.o();
@@ -747,76 +927,31 @@ __device__ __forceinline__ void walk(const typename P::Args& a, typename P::Lds&
             Sy = -oA.y;
             Sz = -oA.z;
             rad2 = rself2;
-            self = true;
-            sbase += 64 * pn;   // (a piece: the next block of its own)
-            if (lane == 0) *nread += (unsigned long long)nuse;
-        } else {
-            // next batch of entries: of this cell, or of its ancestors
-            // (a batch may sweep no records at all)
-            for (;;) {
-                while (g0 >= tot) {
-                    while (e >= e1 && A >= 0) {
-                        A = cA.parent;
-                        if (A >= 0) {
-                            cA = a.cells[A];
-                            L0 = (float)a.sets[cA.set].L0;
-                            e = a.csr_off[A];
-                            e1 = a.csr_off[A + 1];
-                        }
-                    }
-                    if (A < 0) {
-                        done = true;
-                        break;
-                    }
-                    const int n = (int)min(e1 - e, (uint32_t)DBATCH);
-                    bool co_any;
-                    nd = build_sweeps<P, EXT>(a, cA, L0, fr, e, n, bx, hmax, T, &tot, &co_any);
-                    e += n;
-                    g0 = 0;
-                    hold = co_any ? 0 : tot;   // blocks are tested in parts read in cell order only
-                }
-                if (done) break;
-                if (EXT && pn > 1) {
-                    // a piece takes the groups of 64 records k, k + P, ...
-                    const int r = ((g0 >> 6) - pk) % pn;
-                    if (r != 0) g0 += 64 * (pn - (r < 0 ? r + pn : r));
-                    if (g0 >= tot) continue;
-                }
-                if (!EXT || !a.skip || g0 < hold) break;
-                // pass over the blocks of a part read in cell order that lie
-                // beyond the chunk's reach
-                g0 = skip_blocks<P>(a.blkbox, T, nd, g0, lox, loy, loz, bx, hmax, tiny, &hold);
+        } else if (lane < nuse) {
+            const int g = at + lane;
+            int lo = 0, hi = nd - 1;   // the last part starting at or before g
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (T.o[mid] <= g) lo = mid;
+                else hi = mid - 1;
             }
-            // the next 64 records of the batch's sequence
-            if (!done) nuse = min(64, tot - g0);
-            if (lane == 0) *nread += (unsigned long long)nuse;
-            if (lane < nuse) {
-                const int g = g0 + lane;
-                int lo = 0, hi = nd - 1;   // the last part starting at or before g
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (T.o[mid] <= g) lo = mid;
-                    else hi = mid - 1;
-                }
-                const int4 dq = T.q[lo];
-                const float4 df = T.f[lo];
-                const int k = g - T.o[lo];
-                q = (uint32_t)dq.x + (uint32_t)(dq.z >= 0 ? k : dq.y - 1 - k);
-                dl = lo;
-                if (EXT && dq.z == 0) {
-                    pj = a.pos[q];
-                    j = q;
-                    co = true;
-                } else {
-                    pj = a.segpos[q];
-                    j = a.segidx[q];
-                }
-                Sx = df.x;
-                Sy = df.y;
-                Sz = df.z;
-                rad2 = df.w;
+            const int4 dq = T.q[lo];
+            const float4 df = T.f[lo];
+            const int k = g - T.o[lo];
+            q = (uint32_t)dq.x + (uint32_t)(dq.z >= 0 ? k : dq.y - 1 - k);
+            dl = lo;
+            if (EXT && dq.z == 0) {
+                pj = a.pos[q];
+                j = q;
+                co = true;
+            } else {
+                pj = a.segpos[q];
+                j = a.segidx[q];
             }
-            g0 += nuse;
+            Sx = df.x;
+            Sy = df.y;
+            Sz = df.z;
+            rad2 = df.w;
         }
         // the records' own data bound their reach where some part reaches
         // more than 20% beyond the chunk's cutoff, and always in parts read
@@ -836,34 +971,308 @@ __device__ __forceinline__ void walk(const typename P::Args& a, typename P::Lds&
             ok = fmaf(ex, ex, fmaf(ey, ey, ez * ez)) <= rad2;
         }
         const uint64_t okm = __ballot(ok);
-        const int m = __popcll(okm);
-        const int slot = bits_below(okm);
-        const int room = TCAP - fill;
-        if (ok && slot < room) P::stage(S, fill + slot, j, pj, Sx, Sy, Sz, a, pre, early, fr.lo);
-        const int first = min(m, room);
-        fill += first;
-        tself = tself || (self && first > 0);
-        if (done || fill == TCAP) {
-            if (fill > 0) process_tile<P>(S, fill, R, rep, L, acc, tself);
-            fill = 0;
-            tself = false;
+        int m = __popcll(okm);
+        int slot = fill + bits_below(okm);
+        if (W > 1) {
+            if (wi == 0 && skip > 0) {
+                // processed before the walk was parked
+                ok = ok && bits_below(okm) >= skip;
+                slot -= skip;
+                m -= skip;
+            }
+            skip = 0;
+            if (lane == 0) mc[turn * W + wi] = m;
+            __syncthreads();
+            m = 0;
+#pragma unroll 1
+            for (int v = 0; v < W; ++v) {
+                const int c = uni(mc[turn * W + v]);
+                slot += v < wi ? c : 0;
+                nself += ((selfw >> v) & 1) ? c : 0;
+                m += c;
+            }
+            turn ^= 1;
+        } else if (kind == 1) {
+            nself += m;
         }
-        if (done) break;
-        if (ok && slot >= room) {
-            // read again rather than kept through the tile's evaluation
-            if (dl < 0) {
-                const float3 oA = fr.o();
-                P::stage(S, slot - room, q, a.pos[q], -oA.x, -oA.y, -oA.z, a, pre, false, fr.lo);
+        constexpr int cap = TCAP * W;
+        if (ok && slot < cap)
+            P::stage(S, base + (W > 1 ? tile_slot(slot) : slot), j, pj, Sx, Sy, Sz, a, pre, early, fr.lo);
+        const int before = fill;
+        fill += m;
+        if (done || fill >= cap) {
+            if (W > 1) __syncthreads();
+            const int n = min(TCAP, min(fill, cap) - (W > 1 ? TCAP * wi : 0));
+            if (W > 1) {
+                // every wave's tile, whose sums then take the place of its
+                // records; the owner adds them up in the order of the tiles
+                typename P::Acc own;
+                if (n > 0) {
+                    process_tile<P>(S, TILE * wi, n, R, rep, L, own, nself > TCAP * wi);
+                    P::put(S, TILE * wi + lane, own);
+                }
+                __syncthreads();
+                if (wi == 0)
+                    for (int v = 0; v < W && TCAP * v < min(fill, cap); ++v) {
+                        P::get(S, TILE * v + lane, acc);
+                        P::fold(acc, true);
+                    }
+                __syncthreads();
             } else {
-                const float4 df = T.f[dl];
-                const bool cell_order = EXT && T.q[dl].z == 0;
-                const uint32_t jj = cell_order ? q : a.segidx[q];
-                const float4 pq = cell_order ? a.pos[q] : a.segpos[q];
-                P::stage(S, slot - room, jj, pq, df.x, df.y, df.z, a, pre, false, fr.lo);
+                if (n > 0) process_tile<P>(S, base, n, R, rep, L, acc, nself > 0);
+                P::fold(acc, tiles);
+            }
+            fill = max(fill - cap, 0);
+            nself -= cap;
+            if (done) break;
+            if (EXT && W == 1 && may_park && (++seen & 3) == 0 && seen >= PARK_MIN - GRACE &&
+                (late != 0 || handed_out(a))) {
+                late += 4;
+                if (seen >= PARK_MIN && late > GRACE) {
+                    int at_slot = 0;
+                    if (lane == 0) at_slot = atomicAdd(a.taken, 1);
+                    pslot = uni(at_slot);
+                    if (pslot < a.slots) {
+                        cur.kind = kind;
+                        cur.at = at;
+                        cur.skip = cap - before;
+                        cur.A = A;
+                        cur.e0 = e0;
+                        cur.nself = nself - (kind == 1 ? fill : 0);
+                        if (lane == 0) *nread -= (unsigned long long)nuse;
+                        return true;
+                    }
+                    may_park = false;
+                }
+            }
+            if (ok && slot >= cap) {
+                // read again rather than kept through the tile's evaluation
+                const int s2 = base + (W > 1 ? tile_slot(slot - cap) : slot - cap);
+                if (dl < 0) {
+                    const float3 oA = fr.o();
+                    P::stage(S, s2, q, a.pos[q], -oA.x, -oA.y, -oA.z, a, pre, false, fr.lo);
+                } else {
+                    const float4 df = T.f[dl];
+                    const bool cell_order = EXT && T.q[dl].z == 0;
+                    const uint32_t jj = cell_order ? q : a.segidx[q];
+                    const float4 pq = cell_order ? a.pos[q] : a.segpos[q];
+                    P::stage(S, s2, jj, pq, df.x, df.y, df.z, a, pre, false, fr.lo);
+                }
             }
         }
-        fill += m - first;
-        tself = tself || (self && m > first);
+    }
+    return false;
+}
+
+// ---------------------------------------------------------------------------
+// One pass of an interaction stage (density or force): the kernel bodies
+// ---------------------------------------------------------------------------
+template <class P, int W>
+struct PassLds {
+    typename P::template Lds<W> l;
+    SweepTab t[W];
+    int pick[W][64];
+    // the waves' pair evaluations and records loaded (kept in LDS, not in
+    // registers through the walk)
+    unsigned long long cnt[W][2];
+};
+
+// A slot of a parked walk: this header, then the lanes' sums (P::save).
+struct Parked {
+    int leaf, p0, cnt, pad;
+    uint64_t amask, pend;   // the particles of the frame being walked, of the frames to come
+    Frame fr;
+    Cursor cur;
+};
+constexpr int PARK_HEAD = 256;
+static_assert(sizeof(Parked) <= PARK_HEAD && PARK_HEAD + 7 * 64 * sizeof(double) <= PARK_BYTES, "slot layout");
+
+// The frame's particles in the wave's lanes: slot -> particle (the slot-th
+// set bit of amask), R lanes per particle.
+struct Slots {
+    int R, rep, pick;
+    bool act;
+};
+__device__ __forceinline__ Slots take_slots(uint64_t amask, int rmax, int* pick) {
+    const int lane = threadIdx.x & 63;
+    const int nact = __popcll(amask);
+    const int lgR = replicas_lg(nact, rmax), T = 64 >> lgR;
+    const int slot = lane & (T - 1);
+    if ((amask >> lane) & 1ull) pick[bits_below(amask)] = lane;
+    wave_lds_sync();
+    Slots s;
+    s.R = 1 << lgR;
+    s.rep = lane >> (6 - lgR);
+    s.act = slot < nact;
+    s.pick = s.act ? pick[slot] : 0;
+    wave_lds_sync();
+    return s;
+}
+
+// The particles of a chunk to do: all, or the still active ones of a Newton
+// pass (state 1; 2 = waiting for a rebuild; halo particles are never active).
+template <bool SOLVE, class A>
+__device__ __forceinline__ uint64_t to_do(const A& a, int p0, int cnt) {
+    const int lane = threadIdx.x & 63;
+    if (SOLVE) return __ballot(lane < cnt && a.active[p0 + lane] == 1);
+    if (a.owned) return __ballot(lane < cnt && a.owned[p0 + lane] != 0);
+    return cnt >= 64 ? ~0ull : ((1ull << cnt) - 1ull);
+}
+
+// The next frame of a chunk (the lane's particle is read again for every
+// frame rather than kept in registers through the walk).
+template <class P, class A>
+__device__ __forceinline__ uint64_t chunk_frame(const A& a, uint64_t pend, int p0, int cnt, float L0, Frame* fr) {
+    const int lane = threadIdx.x & 63;
+    int q = p0 + (lane < cnt ? lane : 0);
+    asm volatile("" : "+v"(q));
+    return next_frame(pend, a.pos[q], a.plo[q], P::h_of(a, q), L0, fr);
+}
+
+// Persistent: every wave takes chunks until none are left, frame by frame,
+// each frame's particles packed into the first slots.
+template <class P, bool SOLVE, bool EXT>
+__device__ __forceinline__ void run_pass(const typename P::Args& a, PassLds<P, BLK / 64>& M) {
+    const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
+    const int home = blockIdx.x & (NGRP - 1);
+    int grp = 0;
+    int leaf = 0, p0 = 0, cnt = 0;
+    uint64_t pend = 0;   // the chunk's particles in frames to come
+    if (lane == 0) {
+        M.cnt[w][0] = 0ull;
+        M.cnt[w][1] = 0ull;
+    }
+    int pnext = uni(blockIdx.x * (BLK / 64) + w);   // this wave's next piece of a heavy chunk
+    // the current piece: k | P << 5 (1 << 5: a whole chunk) and its slot (-1:
+    // the sums go out directly)
+    int pm = 1 << 5, pslot = -1;
+    for (;;) {
+        if (pend == 0) {
+            int item;
+            pm = 1 << 5;
+            pslot = -1;
+            if (EXT && pnext < a.npieces) {
+                const uint32_t v = a.plist[pnext];
+                item = uni((int)(v >> 5));
+                const int pn = uni((int)a.pcount[item]);
+                if (pn > 1) {
+                    pm = uni((int)(v & 31)) | pn << 5;
+                    pslot = pnext;
+                }
+                pnext += gridDim.x * (BLK / 64);
+            } else {
+                item = next_chunk(a.counter, a.nchunks, a.list, a.lcount, home, grp);
+                if (item < 0) break;
+                if (EXT && a.npieces > 0 && a.pcount[item] != 0) continue;   // handed out as pieces
+            }
+            const int4 ch = a.chunks[item];
+            leaf = uni(ch.x);
+            p0 = uni(ch.y);
+            cnt = uni(ch.z);
+            pend = to_do<SOLVE>(a, p0, cnt);
+            if (pend == 0) continue;
+        }
+        const SetInfo& set = a.sets[a.cells[leaf].set];
+        const bool tiles = EXT && P::kRunning && uni(set.uneven) != 0;   // du and S too tile by tile
+        Frame fr;
+        const uint64_t amask = chunk_frame<P>(a, pend, p0, cnt, (float)set.L0, &fr);
+        pend &= ~amask;
+        const Slots s = take_slots(amask, a.rmax, M.pick[w]);
+        const typename P::Lane L = P::lane(a, p0 + s.pick, s.act, fr);
+        typename P::Acc acc;
+        Cursor cur{};
+        int taken = 0;
+        if (walk<P, EXT, 1>(a, M.l, w * TILE, 0, nullptr, M.t[w], L, acc, leaf, fr, s.R, s.rep, s.act, pm, tiles,
+                            EXT && a.slots > 0 && pslot < 0 && (!P::kRunning || tiles), taken, cur, &M.cnt[w][1])) {
+            char* slot = a.park + (size_t)taken * PARK_BYTES;
+            if (lane == 0) *(Parked*)slot = Parked{leaf, p0, cnt, 0, amask, pend, fr, cur};
+            P::save(acc, (double*)(slot + PARK_HEAD) + lane);
+            pend = 0;
+            continue;
+        }
+        const int nn = P::finish(a, acc, L, p0, s, EXT ? pslot : -1, tiles);
+        const int npair = wave_count(s.act && s.rep == 0 ? nn : 0);
+        if (lane == 0) M.cnt[w][0] += (unsigned long long)npair;
+    }
+    if (lane == 0) {
+        flush_work(a.work, M.cnt[w][0]);
+        flush_work(a.work + 1, M.cnt[w][1]);
+    }
+}
+
+// Blocks as teams: the walks parked by run_pass (DIRECT false), or whole
+// chunks (DIRECT: a tree of uneven sets alone with few chunks, see
+// ensure_state).  The items are taken in turn (block b starts with item b).
+template <class P, bool SOLVE, bool DIRECT, int W>
+__device__ __forceinline__ void run_teams(const typename P::Args& a, PassLds<P, W>& M, int* mc) {
+    const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
+    // (chunks: from the ranges in turn, so that the longest start first)
+    int items = 0;
+    if (!DIRECT) {
+        items = min(uni(*a.taken), a.slots);
+    } else if (a.lcount) {
+        for (int g = 0; g < NGRP; ++g) items = max(items, NGRP * uni(a.lcount[g * CSTRIDE]));
+    } else {
+        items = NGRP * ((a.nchunks + NGRP - 1) / NGRP);
+    }
+    if (lane == 0) {
+        M.cnt[w][0] = 0ull;
+        M.cnt[w][1] = 0ull;
+    }
+    for (int it = blockIdx.x; it < items; it += gridDim.x) {
+        int leaf, p0, cnt;
+        uint64_t pend, amask = 0;
+        Frame fr{};
+        Cursor cur{};
+        typename P::Acc acc;
+        if (!DIRECT) {
+            const char* slot = a.park + (size_t)it * PARK_BYTES;
+            const Parked& k = *(const Parked*)slot;
+            leaf = uni(k.leaf);
+            p0 = uni(k.p0);
+            cnt = uni(k.cnt);
+            amask = uni64(k.amask);
+            pend = uni64(k.pend);
+            fr = Frame{uni(k.fr.kx), uni(k.fr.ky), uni(k.fr.kz), unif(k.fr.g), uni(k.fr.lo) != 0};
+            cur = k.cur;
+            if (w == 0) P::load(acc, (const double*)(slot + PARK_HEAD) + lane);
+        } else {
+            const int g = it & (NGRP - 1), lo = (int)((int64_t)a.nchunks * g / NGRP);
+            const int have = a.lcount ? uni(a.lcount[g * CSTRIDE]) : (int)((int64_t)a.nchunks * (g + 1) / NGRP) - lo;
+            if (it / NGRP >= have) continue;
+            int item = lo + it / NGRP;
+            if (a.list) item = uni((int)a.list[item]);
+            const int4 ch = a.chunks[item];
+            leaf = uni(ch.x);
+            p0 = uni(ch.y);
+            cnt = uni(ch.z);
+            pend = to_do<SOLVE>(a, p0, cnt);
+            if (pend == 0) continue;
+        }
+        for (;;) {
+            if (amask == 0) {
+                amask = chunk_frame<P>(a, pend, p0, cnt, (float)a.sets[a.cells[leaf].set].L0, &fr);
+                pend &= ~amask;
+            }
+            const Slots s = take_slots(amask, a.rmax, M.pick[w]);
+            const typename P::Lane L = P::lane(a, p0 + s.pick, s.act, fr);
+            int none = 0;
+            walk<P, true, W>(a, M.l, 0, w, mc, M.t[w], L, acc, leaf, fr, s.R, s.rep, s.act, 1 << 5, true, false, none,
+                             cur, &M.cnt[w][1]);
+            if (w == 0) {
+                const int nn = P::finish(a, acc, L, p0, s, -1, true);
+                const int npair = wave_count(s.act && s.rep == 0 ? nn : 0);
+                if (lane == 0) M.cnt[w][0] += (unsigned long long)npair;
+            }
+            if (pend == 0) break;
+            amask = 0;   // the chunk's next frame, from its start
+            cur.kind = 0;
+            acc = typename P::Acc{};
+        }
+    }
+    if (lane == 0) {
+        flush_work(a.work, M.cnt[w][0]);
+        flush_work(a.work + 1, M.cnt[w][1]);
     }
 }
 
@@ -873,6 +1282,7 @@ __device__ __forceinline__ void walk(const typename P::Args& a, typename P::Lds&
 template <bool HASH>
 struct DensP {
     using Args = DensArgs;
+    static constexpr bool kRunning = false;   // every sum is added up tile by tile
     struct Lane {
         float4 x;   // position, mass
         float h, hinv;
@@ -884,17 +1294,66 @@ struct DensP {
         uint64_t hs = 0;
     };
     // a tile's partial sums (at most 64 terms per lane) into the FP64 totals
-    static __device__ __forceinline__ void fold(Acc& A) {
+    static __device__ __forceinline__ void fold(Acc& A, bool) {
         A.tf += (double)A.sf;
         A.tg += (double)A.sg;
         A.tw += (double)A.sw;
         A.tq += (double)A.sq;
         A.sf = A.sg = A.sw = A.sq = 0.f;
     }
+    template <int W>
     struct Lds {
-        float4 p[TILE];     // x, y, z (shifted into the target's frame), m
-        uint64_t m[TILE];   // pair-hash terms
+        float4 p[TILE * W];     // x, y, z (shifted into the target's frame), m
+        uint64_t m[TILE * W];   // pair-hash terms
+        int n[TILE * W];        // counts of a tile (put)
     };
+    // a lane's sums and counts of one tile, to LDS and added from there
+    template <int W>
+    static __device__ __forceinline__ void put(Lds<W>& S, int at, const Acc& A) {
+        S.p[at] = make_float4(A.sf, A.sg, A.sw, A.sq);
+        S.n[at] = A.nn;
+        if (HASH) S.m[at] = A.hs;
+    }
+    template <int W>
+    static __device__ __forceinline__ void get(const Lds<W>& S, int at, Acc& A) {
+        const float4 v = S.p[at];
+        A.sf = v.x;
+        A.sg = v.y;
+        A.sw = v.z;
+        A.sq = v.w;
+        A.nn += S.n[at];
+        if (HASH) A.hs += S.m[at];
+    }
+    // the sums of a parked walk (at tile boundaries), a lane's every 64th
+    static __device__ __forceinline__ void save(const Acc& A, double* q) {
+        q[0] = A.tf;
+        q[64] = A.tg;
+        q[128] = A.tw;
+        q[192] = A.tq;
+        q[256] = (double)A.nn;
+        if (HASH) q[320] = __longlong_as_double((long long)A.hs);
+    }
+    static __device__ __forceinline__ void load(Acc& A, const double* q) {
+        A.tf = q[0];
+        A.tg = q[64];
+        A.tw = q[128];
+        A.tq = q[192];
+        A.nn = (int)q[256];
+        if (HASH) A.hs = (uint64_t)__double_as_longlong(q[320]);
+    }
+    static __device__ __forceinline__ float h_of(const Args& a, int p) { return a.ph[p]; }
+    // the lane's particle in the frame; an idle lane sits far away so no
+    // record is ever in its range
+    static __device__ __forceinline__ Lane lane(const Args& a, int p, bool act, const Frame& fr) {
+        Lane L;
+        L.x = act ? in_frame(a.pos[p], fr.lo ? a.plo[p] : make_float4(0.f, 0.f, 0.f, 0.f), fr.o())
+                  : make_float4(-FAR, -FAR, -FAR, 0.f);
+        L.h = act ? a.ph[p] : 1.f;
+        L.hinv = 1.f / L.h;
+        return L;
+    }
+    static __device__ __forceinline__ int finish(const Args& a, const Acc& acc, const Lane& L, int p0, const Slots& s,
+                                                 int pslot, bool);
     static __device__ __forceinline__ float cut(float hmax, float) { return hmax; }
     // squared cutoff of a pair: the target's h (density gathers over h_i)
     static __device__ __forceinline__ float lim2(float hi2, float) { return hi2; }
@@ -905,13 +1364,15 @@ struct DensP {
     static __device__ __forceinline__ Pre pre(const Args&, uint32_t, bool) { return Pre{}; }
     static __device__ __forceinline__ float rad2(float part2, const Pre&, float, float) { return part2; }
     static __device__ __forceinline__ float blk_rad2(float part2, float, float, float) { return part2; }
-    static __device__ __forceinline__ void stage(Lds& S, int slot, uint32_t j, const float4& pj, float Sx, float Sy,
+    template <int W>
+    static __device__ __forceinline__ void stage(Lds<W>& S, int slot, uint32_t j, const float4& pj, float Sx, float Sy,
                                                  float Sz, const Args& a, const Pre&, bool, bool uselo) {
         const float4 lo = uselo ? a.plo[j] : make_float4(0.f, 0.f, 0.f, 0.f);
         S.p[slot] = make_float4((pj.x + Sx) + lo.x, (pj.y + Sy) + lo.y, (pj.z + Sz) + lo.z, pj.w);
         if (HASH) S.m[slot] = a.mix[j];
     }
-    static __device__ __forceinline__ void pair(Acc& A, const Lds& S, int j, const Lane& L) {
+    template <int W>
+    static __device__ __forceinline__ void pair(Acc& A, const Lds<W>& S, int j, const Lane& L) {
         const float4 q = S.p[j];
         const float dx = L.x.x - q.x, dy = L.x.y - q.y, dz = L.x.z - q.z;
         const float r = fsqrt(fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
@@ -946,117 +1407,47 @@ __device__ __forceinline__ void dens_write(const DensArgs& a, int p, float hi, f
     if (HASH) a.hash[p] = hs;
 }
 
-// EXT: the tree may have heavy chunks or partners read in cell order (the
-// kernel without that code keeps more registers for the common case).
+// The outputs of a frame's particles (or their partial sums to a piece's
+// slot); returns the lane's neighbour count.
+template <bool HASH>
+__device__ __forceinline__ int DensP<HASH>::finish(const DensArgs& a, const Acc& acc, const Lane& L, int p0,
+                                                   const Slots& s, int pslot, bool) {
+    const int R = s.R;
+    const double sf = comb_d(acc.tf, R), sg = comb_d(acc.tg, R);
+    const double sw = comb_d(acc.tw, R), sq = comb_d(acc.tq, R);
+    const int nn = comb_i(acc.nn, R);
+    const uint64_t hs = HASH ? comb_u64(acc.hs, R) : 0ull;
+    if (s.act && s.rep == 0) {
+        if (pslot >= 0) {
+            double* q = a.part + (size_t)pslot * PART_WORDS * CHUNK + s.pick;
+            q[0 * CHUNK] = sf;
+            q[1 * CHUNK] = sg;
+            q[2 * CHUNK] = sw;
+            q[3 * CHUNK] = sq;
+            q[4 * CHUNK] = (double)nn;
+            q[5 * CHUNK] = __longlong_as_double((long long)hs);
+        } else {
+            dens_write<HASH>(a, p0 + s.pick, L.h, L.x.w, sf, sg, sw, sq, nn, hs);
+        }
+    }
+    return nn;
+}
+
+// EXT: the tree may have heavy chunks, long walks or partners read in cell
+// order (the kernel without that code keeps more registers for the common
+// case).
 template <bool SOLVE, bool HASH, bool EXT>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(5))) void k_density(DensArgs a) {
-    using P = DensP<HASH>;
-    __shared__ typename P::Lds s_l[BLK / 64];
-    __shared__ SweepTab s_t[BLK / 64];
-    __shared__ int s_pick[BLK / 64][64];
-    // the wave's pair evaluations and records loaded (kept in LDS, not in
-    // registers through the walk)
-    __shared__ unsigned long long s_cnt[BLK / 64][2];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    typename P::Lds& S = s_l[w];
-    const int home = blockIdx.x & (NGRP - 1);
-    int grp = 0;
-    // one step per frame of a chunk: the particles of the chunk that take
-    // part -- all, or the still active ones of a Newton pass (state 1; 2 =
-    // parked until a rebuild) -- are done frame by frame (pend: those left),
-    // each frame's packed into the first slots
-    int leaf = 0, p0 = 0, cnt = 0;
-    uint64_t pend = 0;
-    if (lane == 0) {
-        s_cnt[w][0] = 0ull;
-        s_cnt[w][1] = 0ull;
-    }
-    int pnext = uni(blockIdx.x * (BLK / 64) + w);   // this wave's next piece of a heavy chunk
-    // the current piece: k | P << 5 (1 << 5: a whole chunk) and its slot (-1:
-    // the sums go out directly)
-    int pm = 1 << 5, pslot = -1;
-    for (;;) {
-        if (pend == 0) {
-            int item;
-            pm = 1 << 5;
-            pslot = -1;
-            if (EXT && pnext < a.npieces) {
-                const uint32_t v = a.plist[pnext];
-                item = uni((int)(v >> 5));
-                const int pn = uni((int)a.pcount[item]);
-                if (pn > 1) {
-                    pm = uni((int)(v & 31)) | pn << 5;
-                    pslot = pnext;
-                }
-                pnext += gridDim.x * (BLK / 64);
-            } else {
-                item = next_chunk(a.counter, a.nchunks, a.list, a.lcount, home, grp);
-                if (item < 0) break;
-                if (EXT && a.npieces > 0 && a.pcount[item] != 0) continue;   // handed out as pieces
-            }
-            const int4 ch = a.chunks[item];
-            leaf = uni(ch.x);
-            p0 = uni(ch.y);
-            cnt = uni(ch.z);
-            pend = cnt >= 64 ? ~0ull : ((1ull << cnt) - 1ull);
-            if (SOLVE) pend = __ballot(lane < cnt && a.active[p0 + lane] == 1);   // (halo: never active)
-            else if (a.owned) pend = __ballot(lane < cnt && a.owned[p0 + lane] != 0);
-            if (pend == 0) continue;
-        }
-        const float L0 = (float)a.sets[a.cells[leaf].set].L0;
-        Frame fr;
-        uint64_t amask;
-        {
-            // the lane's particle, read again for every frame rather than
-            // kept in registers through the walk
-            int q = p0 + (lane < cnt ? lane : 0);
-            asm volatile("" : "+v"(q));
-            amask = next_frame(pend, a.pos[q], a.plo[q], a.ph[q], L0, &fr);
-        }
-        pend &= ~amask;
-        const int nact = __popcll(amask);
-        const int lgR = replicas_lg(nact, a.rmax), R = 1 << lgR, T = 64 >> lgR;
-        const int slot = lane & (T - 1), rep = lane >> (6 - lgR);
-        // slot -> particle: the slot-th set bit of amask
-        if ((amask >> lane) & 1ull) s_pick[w][bits_below(amask)] = lane;
-        wave_lds_sync();
-        const int pick = slot < nact ? s_pick[w][slot] : 0;
-        wave_lds_sync();
-        const int p = p0 + pick;
-        const bool act = slot < nact;
-        typename P::Lane L;
-        // an idle lane sits far away so no record is ever in its range
-        L.x = act ? in_frame(a.pos[p], fr.lo ? a.plo[p] : make_float4(0.f, 0.f, 0.f, 0.f), fr.o())
-                  : make_float4(-FAR, -FAR, -FAR, 0.f);
-        L.h = act ? a.ph[p] : 1.f;
-        L.hinv = 1.f / L.h;
-        typename P::Acc acc;
-        walk<P, EXT>(a, S, s_t[w], L, acc, leaf, fr, R, rep, act, pm, &s_cnt[w][1]);
+    __shared__ PassLds<DensP<HASH>, BLK / 64> s_m;
+    run_pass<DensP<HASH>, SOLVE, EXT>(a, s_m);
+}
 
-        const double sf = comb_d(acc.tf, R), sg = comb_d(acc.tg, R);
-        const double sw = comb_d(acc.tw, R), sq = comb_d(acc.tq, R);
-        const int nn = comb_i(acc.nn, R);
-        const uint64_t hs = HASH ? comb_u64(acc.hs, R) : 0ull;
-        if (act && rep == 0) {
-            if (EXT && pslot >= 0) {
-                double* q = a.part + (size_t)pslot * PART_WORDS * CHUNK + pick;
-                q[0 * CHUNK] = sf;
-                q[1 * CHUNK] = sg;
-                q[2 * CHUNK] = sw;
-                q[3 * CHUNK] = sq;
-                q[4 * CHUNK] = (double)nn;
-                q[5 * CHUNK] = __longlong_as_double((long long)hs);
-            } else {
-                dens_write<HASH>(a, p, L.h, L.x.w, sf, sg, sw, sq, nn, hs);
-            }
-        }
-        const int npair = wave_count(act && rep == 0 ? nn : 0);
-        if (lane == 0) s_cnt[w][0] += (unsigned long long)npair;
-    }
-    if (lane == 0) {
-        flush_work(a.work, s_cnt[w][0]);
-        flush_work(a.work + 1, s_cnt[w][1]);
-    }
+// (few teams run at a time: registers rather than waves)
+template <bool SOLVE, bool HASH, bool DIRECT, int W>
+__global__ __launch_bounds__(64 * W) void k_density_teams(DensArgs a) {
+    __shared__ PassLds<DensP<HASH>, W> s_m;
+    __shared__ int s_mc[2 * W];
+    run_teams<DensP<HASH>, SOLVE, DIRECT, W>(a, s_m, s_mc);
 }
 
 // Split chunks: the partial sums of the pieces, added in piece order, give
@@ -1102,6 +1493,9 @@ struct ForceArgs {
     const float4* pv;
     const float4* frec;   // h, A, sound speed, K = 8/(pi h^5); pv.w holds rho
     const uint8_t* owned;
+    const uint8_t* active;  // (null: as the chunk list, of the density's Newton passes)
+    const uint32_t* list;
+    const int* lcount;
     const uint64_t* mix;
     const uint64_t* csr;
     const uint32_t* csr_off;
@@ -1116,6 +1510,9 @@ struct ForceArgs {
     const uint32_t* plist;  // the pieces (chunk << 5 | piece), handed out first
     int npieces;
     double* part;           // partial sums of the pieces of split chunks
+    char* park;             // slots of parked walks (see walk), how many there are,
+    int slots;
+    int* taken;             // how many were asked for in this pass (zero at launch)
     float alpha;
     float *ax, *ay, *az, *du, *vsig, *S;
     int32_t* nf;
@@ -1134,30 +1531,140 @@ __device__ __forceinline__ float gradF(float q, float h, float rinv) {
 template <bool HASH>
 struct ForceP {
     using Args = ForceArgs;
+    static constexpr bool kRunning = true;   // du and S may run on over the tiles (see fold)
     struct Lane {
         float4 x;   // position, mass
         float4 v;   // velocity, rho
         float h, hinv, K, A, c, alpha;
     };
     struct Acc {
-        float ax = 0, ay = 0, az = 0, du = 0, vs = 0, S = 0;   // a: over one tile; du, vs, S: over all
-        double tx = 0, ty = 0, tz = 0;                         // a over the tiles done
+        float ax = 0, ay = 0, az = 0, du = 0, S = 0, vs = 0;   // sums over one tile (du, S: see fold); vs: over all
+        double tx = 0, ty = 0, tz = 0, tu = 0, tS = 0;         // the sums over the tiles done
         int nn = 0;
         uint64_t hs = 0;
     };
-    static __device__ __forceinline__ void fold(Acc& A) {
+    // The acceleration is added up in FP64 over the tiles.  du and S run on
+    // in FP32 in a set of one level, whose walks are short; in an uneven set
+    // (tiles) they are added up like the acceleration, as a walk that several
+    // waves share needs it.  It goes by the particle's set alone, so that a
+    // set's results do not depend on who walks a chunk or on a batch's other
+    // sets.
+    static __device__ __forceinline__ void fold(Acc& A, bool tiles) {
+        if (tiles) {
+            A.tu += (double)A.du;
+            A.tS += (double)A.S;
+            A.du = A.S = 0.f;
+        }
         A.tx += (double)A.ax;
         A.ty += (double)A.ay;
         A.tz += (double)A.az;
         A.ax = A.ay = A.az = 0.f;
     }
+    template <int W>
     struct Lds {
-        float4 p[TILE];    // x, y, z (shifted into the target's frame), h
-        float4 h[TILE];    // m, 1/h, K = 8/(pi h^5), A
-        float4 v[TILE];    // vx, vy, vz, rho
-        float c[TILE];     // sound speed
-        uint64_t m[TILE];  // pair-hash terms
+        float4 p[TILE * W];    // x, y, z (shifted into the target's frame), h
+        float4 h[TILE * W];    // m, 1/h, K = 8/(pi h^5), A
+        float4 v[TILE * W];    // vx, vy, vz, rho
+        float c[TILE * W];     // sound speed
+        uint64_t m[TILE * W];  // pair-hash terms
     };
+    // a lane's sums and counts of one tile, to LDS and added from there
+    template <int W>
+    static __device__ __forceinline__ void put(Lds<W>& S, int at, const Acc& A) {
+        S.p[at] = make_float4(A.ax, A.ay, A.az, A.du);
+        S.h[at] = make_float4(A.S, A.vs, __int_as_float(A.nn), 0.f);
+        if (HASH) S.m[at] = A.hs;
+    }
+    template <int W>
+    static __device__ __forceinline__ void get(const Lds<W>& S, int at, Acc& A) {
+        const float4 v = S.p[at], u = S.h[at];
+        A.ax = v.x;
+        A.ay = v.y;
+        A.az = v.z;
+        A.du = v.w;
+        A.S = u.x;
+        A.vs = fmaxf(A.vs, u.y);
+        A.nn += __float_as_int(u.z);
+        if (HASH) A.hs += S.m[at];
+    }
+    // the sums of a parked walk (at tile boundaries), a lane's every 64th
+    static __device__ __forceinline__ void save(const Acc& A, double* q) {
+        q[0] = A.tx;
+        q[64] = A.ty;
+        q[128] = A.tz;
+        q[192] = A.tu;
+        q[256] = A.tS;
+        q[320] = __hiloint2double(__float_as_int(A.vs), A.nn);
+        if (HASH) q[384] = __longlong_as_double((long long)A.hs);
+    }
+    static __device__ __forceinline__ void load(Acc& A, const double* q) {
+        A.tx = q[0];
+        A.ty = q[64];
+        A.tz = q[128];
+        A.tu = q[192];
+        A.tS = q[256];
+        A.vs = __int_as_float(__double2hiint(q[320]));
+        A.nn = __double2loint(q[320]);
+        if (HASH) A.hs = (uint64_t)__double_as_longlong(q[384]);
+    }
+    static __device__ __forceinline__ float h_of(const Args& a, int p) { return a.frec[p].x; }
+    // the lane's particle in the frame, from the same records as the staged
+    // partners (the two sides of a pair see identical values); an idle lane
+    // sits far away so no record is ever in its range
+    static __device__ __forceinline__ Lane lane(const Args& a, int p, bool act, const Frame& fr) {
+        Lane L;
+        L.x = act ? in_frame(a.pos[p], fr.lo ? a.plo[p] : make_float4(0.f, 0.f, 0.f, 0.f), fr.o())
+                  : make_float4(-FAR, -FAR, -FAR, 0.f);
+        const float4 fi = act ? a.frec[p] : make_float4(1.f, 0.f, 0.f, 0.f);
+        L.h = fi.x;
+        L.hinv = frcp(L.h);
+        L.K = fi.w;
+        L.v = act ? a.pv[p] : make_float4(0.f, 0.f, 0.f, 1.f);
+        L.A = fi.y;
+        L.c = fi.z;
+        L.alpha = a.alpha;
+        return L;
+    }
+    static __device__ __forceinline__ int finish(const Args& a, const Acc& acc, const Lane&, int p0, const Slots& s,
+                                                 int pslot, bool tiles) {
+        const int R = s.R, p = p0 + s.pick;
+        double du, Ss;
+        if (tiles) {
+            du = comb_d(acc.tu, R);
+            Ss = comb_d(acc.tS, R);
+        } else {
+            du = (double)comb_f(acc.du, R);
+            Ss = (double)comb_f(acc.S, R);
+        }
+        const float vs = comb_max(acc.vs, R);
+        const int nn = comb_i(acc.nn, R);
+        const uint64_t hs = HASH ? comb_u64(acc.hs, R) : 0ull;
+        const double tx = comb_d(acc.tx, R), ty = comb_d(acc.ty, R), tz = comb_d(acc.tz, R);
+        if (s.act && s.rep == 0) {
+            if (pslot >= 0) {
+                // a piece: its FP64 sums to its slot
+                double* q = a.part + (size_t)pslot * PART_WORDS * CHUNK + s.pick;
+                q[0 * CHUNK] = tx;
+                q[1 * CHUNK] = ty;
+                q[2 * CHUNK] = tz;
+                q[3 * CHUNK] = du;
+                q[4 * CHUNK] = (double)vs;
+                q[5 * CHUNK] = Ss;
+                q[6 * CHUNK] = (double)nn;
+                q[7 * CHUNK] = __longlong_as_double((long long)hs);
+            } else {
+                a.ax[p] = (float)tx;
+                a.ay[p] = (float)ty;
+                a.az[p] = (float)tz;
+                a.du[p] = (float)du;
+                a.vsig[p] = vs;
+                a.S[p] = (float)Ss;
+                a.nf[p] = nn;
+                if (HASH) a.hash[p] = hs;
+            }
+        }
+        return nn;
+    }
     static __device__ __forceinline__ float cut(float hmax, float hpart) { return fmaxf(hmax, hpart); }
     // squared cutoff of a pair: max(h_i, h_j)
     static __device__ __forceinline__ float lim2(float hi2, float hj) { return fmaxf(hi2, hj * hj); }
@@ -1182,7 +1689,8 @@ struct ForceP {
         const float r = fmaf(fmaxf(hmax, hb), 1.000002f, tiny);
         return fminf(part2, r * r);
     }
-    static __device__ __forceinline__ void stage(Lds& S, int slot, uint32_t j, const float4& pj, float Sx, float Sy,
+    template <int W>
+    static __device__ __forceinline__ void stage(Lds<W>& S, int slot, uint32_t j, const float4& pj, float Sx, float Sy,
                                                  float Sz, const Args& a, const Pre& pr, bool loaded, bool uselo) {
         const float4 fj = loaded ? pr.f : a.frec[j];
         const float4 lo = uselo ? a.plo[j] : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1192,7 +1700,8 @@ struct ForceP {
         S.c[slot] = fj.z;
         if (HASH) S.m[slot] = a.mix[j];
     }
-    static __device__ __forceinline__ void pair(Acc& A, const Lds& S, int j, const Lane& L) {
+    template <int W>
+    static __device__ __forceinline__ void pair(Acc& A, const Lds<W>& S, int j, const Lane& L) {
         const float4 q = S.p[j];
         const float4 sh = S.h[j];
         const float4 sv = S.v[j];
@@ -1229,132 +1738,15 @@ struct ForceP {
 
 template <bool HASH, bool EXT>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(5))) void k_force(ForceArgs a) {
-    using P = ForceP<HASH>;
-    __shared__ typename P::Lds s_l[BLK / 64];
-    __shared__ SweepTab s_t[BLK / 64];
-    __shared__ int s_pick[BLK / 64][64];
-    // the wave's pair evaluations and records loaded (kept in LDS, not in
-    // registers through the walk)
-    __shared__ unsigned long long s_cnt[BLK / 64][2];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    typename P::Lds& S = s_l[w];
-    const int home = blockIdx.x & (NGRP - 1);
-    int grp = 0;
-    // one step per frame of a chunk (pend: the chunk's particles left, each
-    // frame's packed into the first slots)
-    int leaf = 0, p0 = 0, cnt = 0;
-    uint64_t pend = 0;
-    if (lane == 0) {
-        s_cnt[w][0] = 0ull;
-        s_cnt[w][1] = 0ull;
-    }
-    int pnext = uni(blockIdx.x * (BLK / 64) + w);   // this wave's next piece of a heavy chunk
-    // the current piece: k | P << 5 (1 << 5: a whole chunk) and its slot (-1:
-    // the sums go out directly)
-    int pm = 1 << 5, pslot = -1;
-    for (;;) {
-        if (pend == 0) {
-            int item;
-            pm = 1 << 5;
-            pslot = -1;
-            if (EXT && pnext < a.npieces) {
-                const uint32_t v = a.plist[pnext];
-                item = uni((int)(v >> 5));
-                const int pn = uni((int)a.pcount[item]);
-                if (pn > 1) {
-                    pm = uni((int)(v & 31)) | pn << 5;
-                    pslot = pnext;
-                }
-                pnext += gridDim.x * (BLK / 64);
-            } else {
-                item = next_chunk(a.counter, a.nchunks, nullptr, nullptr, home, grp);
-                if (item < 0) break;
-                if (EXT && a.npieces > 0 && a.pcount[item] != 0) continue;   // handed out as pieces
-            }
-            const int4 ch = a.chunks[item];
-            leaf = uni(ch.x);
-            p0 = uni(ch.y);
-            cnt = uni(ch.z);
-            pend = cnt >= 64 ? ~0ull : ((1ull << cnt) - 1ull);
-            if (a.owned) pend = __ballot(lane < cnt && a.owned[p0 + lane] != 0);
-            if (pend == 0) continue;
-        }
-        const float L0 = (float)a.sets[a.cells[leaf].set].L0;
-        Frame fr;
-        uint64_t amask;
-        {
-            // the lane's particle, read again for every frame rather than
-            // kept in registers through the walk
-            int q = p0 + (lane < cnt ? lane : 0);
-            asm volatile("" : "+v"(q));
-            amask = next_frame(pend, a.pos[q], a.plo[q], a.frec[q].x, L0, &fr);
-        }
-        pend &= ~amask;
-        const int nact = __popcll(amask);
-        const int lgR = replicas_lg(nact, a.rmax), R = 1 << lgR, T = 64 >> lgR;
-        const int slot = lane & (T - 1), rep = lane >> (6 - lgR);
-        if ((amask >> lane) & 1ull) s_pick[w][bits_below(amask)] = lane;
-        wave_lds_sync();
-        const int pick = slot < nact ? s_pick[w][slot] : 0;
-        wave_lds_sync();
-        const int p = p0 + pick;
-        const bool act = slot < nact;
-        typename P::Lane L;
-        // an idle lane sits far away so no record is ever in its range
-        L.x = act ? in_frame(a.pos[p], fr.lo ? a.plo[p] : make_float4(0.f, 0.f, 0.f, 0.f), fr.o())
-                  : make_float4(-FAR, -FAR, -FAR, 0.f);
-        // the same records as the staged partners: the two sides of a pair
-        // see identical values
-        const float4 fi = act ? a.frec[p] : make_float4(1.f, 0.f, 0.f, 0.f);
-        L.h = fi.x;
-        L.hinv = frcp(L.h);
-        L.K = fi.w;
-        L.v = act ? a.pv[p] : make_float4(0.f, 0.f, 0.f, 1.f);
-        L.A = fi.y;
-        L.c = fi.z;
-        L.alpha = a.alpha;
-        typename P::Acc acc;
-        walk<P, EXT>(a, S, s_t[w], L, acc, leaf, fr, R, rep, act, pm, &s_cnt[w][1]);
+    __shared__ PassLds<ForceP<HASH>, BLK / 64> s_m;
+    run_pass<ForceP<HASH>, false, EXT>(a, s_m);
+}
 
-        const float du = comb_f(acc.du, R);
-        const float vs = comb_max(acc.vs, R), Ss = comb_f(acc.S, R);
-        const int nn = comb_i(acc.nn, R);
-        const uint64_t hs = HASH ? comb_u64(acc.hs, R) : 0ull;
-        if (EXT && pslot >= 0) {
-            // a piece: its FP64 sums to its slot
-            const double tx = comb_d(acc.tx, R), ty = comb_d(acc.ty, R), tz = comb_d(acc.tz, R);
-            if (act && rep == 0) {
-                double* q = a.part + (size_t)pslot * PART_WORDS * CHUNK + pick;
-                q[0 * CHUNK] = tx;
-                q[1 * CHUNK] = ty;
-                q[2 * CHUNK] = tz;
-                q[3 * CHUNK] = (double)du;
-                q[4 * CHUNK] = (double)vs;
-                q[5 * CHUNK] = (double)Ss;
-                q[6 * CHUNK] = (double)nn;
-                q[7 * CHUNK] = __longlong_as_double((long long)hs);
-            }
-        } else {
-            const float ax = (float)comb_d(acc.tx, R), ay = (float)comb_d(acc.ty, R);
-            const float az = (float)comb_d(acc.tz, R);
-            if (act && rep == 0) {
-                a.ax[p] = ax;
-                a.ay[p] = ay;
-                a.az[p] = az;
-                a.du[p] = du;
-                a.vsig[p] = vs;
-                a.S[p] = Ss;
-                a.nf[p] = nn;
-                if (HASH) a.hash[p] = hs;
-            }
-        }
-        const int npair = wave_count(act && rep == 0 ? nn : 0);
-        if (lane == 0) s_cnt[w][0] += (unsigned long long)npair;
-    }
-    if (lane == 0) {
-        flush_work(a.work, s_cnt[w][0]);
-        flush_work(a.work + 1, s_cnt[w][1]);
-    }
+template <bool HASH, bool DIRECT, int W>
+__global__ __launch_bounds__(64 * W) void k_force_teams(ForceArgs a) {
+    __shared__ PassLds<ForceP<HASH>, W> s_m;
+    __shared__ int s_mc[2 * W];
+    run_teams<ForceP<HASH>, false, DIRECT, W>(a, s_m, s_mc);
 }
 
 template <bool HASH>
@@ -1400,6 +1792,14 @@ __global__ __launch_bounds__(256) void k_force_pieces(ForceArgs a) {
 __global__ void k_zero_i32(int32_t* p, int n) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
+}
+
+// The work counters of an interaction pass, and the slots taken (after a
+// Newton step k_newton has cleared them).
+__global__ void k_zero_ctr(int32_t* p, int n, int32_t* taken) {
+    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0;
+    if (i == n) *taken = 0;
 }
 
 __global__ void k_solve_init(int64_t n, const uint8_t* __restrict__ owned, uint8_t* active, float* lo, float* hi,
@@ -1489,11 +1889,15 @@ __device__ __forceinline__ bool newton_step(int64_t p, uint8_t* __restrict__ act
 
 // The step of every active particle (one thread each); the rare rebuild
 // flags.  The particles still active are counted afterwards (k_count_active).
-__global__ void k_newton(int64_t n, const SetInfo* __restrict__ sets, int nsets, uint8_t* __restrict__ active,
+// Also clears the work counters (ctr words of ctr) for the next density pass.
+__global__ void k_newton(int64_t n, int32_t* __restrict__ ctr, int nctr, int32_t* __restrict__ taken,
+                         const SetInfo* __restrict__ sets, int nsets, uint8_t* __restrict__ active,
                          const float* __restrict__ nw, const float* __restrict__ dnw, float* __restrict__ ph,
                          const float* __restrict__ bound, float* __restrict__ lo, float* __restrict__ hi,
                          float* __restrict__ dstep, double target, double tol, int32_t* __restrict__ status) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = p; i < nctr; i += (int64_t)gridDim.x * blockDim.x) ctr[i] = 0;
+    if (p == 0) *taken = 0;
     if (p >= n || active[p] != 1) return;
     const int s = set_of(sets, nsets, p);
     bool rebuild = false;
@@ -1773,7 +2177,7 @@ static inline unsigned nblk(int64_t n, int bs) { return (unsigned)((n + bs - 1) 
         if (e_.st != SPH_OK) return e_; \
     } while (0)
 
-static Err ensure_state(sph_tree* t) {
+static Err ensure_state(const sph_ctx* ctx, sph_tree* t) {
     const int64_t n = std::max<int64_t>(t->n, 1);
     void* p;
     // density: rho, drho, nw, dnw (float), nngb (int), hash (u64)
@@ -1809,6 +2213,13 @@ static Err ensure_state(sph_tree* t) {
     t->fvs = t->fdu + n;
     t->fS = t->fvs + n;
     t->fn = (int32_t*)(t->fS + n);
+    // who walks the chunks (see walk): teams from the start where every set is
+    // uneven and there are no more chunks than waves fit; else waves, with slots
+    // for the walks they park, where the tree has long walks at all.  More than PARK_SLOTS
+    // walks (eight per CU) parked at a time would be no tail.
+    t->direct = t->ext() && t->nplain == 0 && t->npieces == 0 && t->nchunks <= 20 * (int64_t)ctx->n_cu;
+    t->nslots = t->ext() && !t->direct ? std::min<int64_t>(t->nchunks, PARK_SLOTS) : 0;
+    if (t->nslots > 0 && !t->try_alloc(t->b_park, (size_t)PARK_BYTES * t->nslots, &p)) t->nslots = 0;
     // reduction chunks: RED_CHUNK particles of one set each
     if (t->red_off != t->off) {
         t->red_chunks.clear();
@@ -1880,7 +2291,7 @@ static DensArgs dens_args(sph_tree* t, int* counter, const int* lcount) {
     a.mix = t->mix;
     a.active = t->active;
     a.owned = t->owned;
-    a.list = lcount ? t->alist : nullptr;
+    a.list = lcount ? t->alist : t->order;
     a.lcount = lcount;
     a.csr = t->csr;
     a.csr_off = t->csr_off;
@@ -1894,6 +2305,8 @@ static DensArgs dens_args(sph_tree* t, int* counter, const int* lcount) {
     a.plist = t->plist;
     a.npieces = (int)t->npieces;
     a.part = t->part;
+    a.park = (char*)t->b_park.p;
+    a.slots = (int)t->nslots;
     a.segidx = t->segidx;
     a.status = t->status;
     a.rho = t->rho;
@@ -1904,27 +2317,53 @@ static DensArgs dens_args(sph_tree* t, int* counter, const int* lcount) {
     a.hash = t->hashd;
     a.work = (unsigned long long*)(t->work_ctr);
     a.rmax = rmax_of(t);
+    a.taken = nullptr;
     return a;
+}
+
+// A team kernel over items chunks or parked walks: a block per item, at most
+// as many as fit at once.  Eight waves a block where that leaves blocks idle
+// otherwise (30011 particles, 597 chunks: 1.05 ms for the whole pass over
+// density and force against 1.12 with four and 1.15 with sixteen), four
+// where the chunks are more than fit (200000 particles, 4819 chunks: 5.0
+// against 5.6 ms).
+template <class A, class F>
+static void launch_teams(const sph_ctx* ctx, const sph_tree* t, const A& a, int64_t items, F kern) {
+    const bool wide = items <= 4 * (int64_t)ctx->n_cu || !t->direct;
+    int bpc = wide ? 2 : 4;
+    if (t->prm.blocks_per_cu > 0) bpc = std::min(bpc, t->prm.blocks_per_cu);
+    const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(items, (int64_t)ctx->n_cu * bpc)));
+    if (wide) hipLaunchKernelGGL(kern(std::integral_constant<int, 8>{}), grid, dim3(512), 0, ctx->stream, a);
+    else hipLaunchKernelGGL(kern(std::integral_constant<int, 4>{}), grid, dim3(256), 0, ctx->stream, a);
 }
 
 // listed: a Newton pass after the first, over the chunks that still hold
 // active particles (k_chunk_list; its counts sit in the context's counter
-// block after the force counters, zeroed here with the density counters)
+// block after the force counters; the Newton step cleared them all)
 static bool ext_kernels(const sph_tree* t) { return t->ext(); }
 
 static void launch_density(sph_ctx* ctx, sph_tree* t, bool solve, bool listed, int* counter) {
     hipStream_t st = ctx->stream;
     int* lcount = nullptr;
+    int* taken = ctx->d_counter + sph_ctx::CTR_PARK;
     if (listed) {
         lcount = counter + 2 * NGRP * CSTRIDE;
-        hipLaunchKernelGGL(k_zero_i32, dim3(3), dim3(256), 0, st, counter, 3 * NGRP * CSTRIDE);
         const int bpg = (int)((t->nchunks / NGRP + LIST_BS) / LIST_BS);
         hipLaunchKernelGGL(k_chunk_list, dim3(NGRP * bpg), dim3(LIST_BS), 0, st, t->chunks, (int)t->nchunks, bpg,
-                           t->active, t->alist, lcount);
+                           t->active, t->order, t->alist, lcount);
     } else {
-        hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(256), 0, st, counter, NGRP * CSTRIDE);
+        hipLaunchKernelGGL(k_zero_ctr, dim3(2), dim3(256), 0, st, counter, NGRP * CSTRIDE, taken);
     }
     DensArgs a = dens_args(t, counter, lcount);
+    a.taken = taken;
+    if (t->direct) {
+        launch_teams(ctx, t, a, t->nchunks, [&](auto W) {
+            constexpr int w = decltype(W)::value;
+            return solve ? (t->hash ? k_density_teams<true, true, true, w> : k_density_teams<true, false, true, w>)
+                         : (t->hash ? k_density_teams<false, true, true, w> : k_density_teams<false, false, true, w>);
+        });
+        return;
+    }
     void (*kern)(DensArgs);
     if (ext_kernels(t)) {
         if (solve) kern = t->hash ? k_density<true, true, true> : k_density<true, false, true>;
@@ -1934,6 +2373,11 @@ static void launch_density(sph_ctx* ctx, sph_tree* t, bool solve, bool listed, i
         else kern = t->hash ? k_density<false, true, false> : k_density<false, false, false>;
     }
     hipLaunchKernelGGL(kern, dim3(persistent_blocks(ctx, t, t->nchunks, (const void*)kern)), dim3(BLK), 0, st, a);
+    if (t->nslots > 0)
+        launch_teams(ctx, t, a, t->nslots, [&](auto W) {
+            constexpr int w = decltype(W)::value;
+            return t->hash ? k_density_teams<false, true, false, w> : k_density_teams<false, false, false, w>;
+        });
     if (t->npieces > 0) {
         const dim3 gp(nblk(t->npieces, 4));
         if (solve) {
@@ -1969,9 +2413,11 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     if (t->blkbox && t->ext())
         hipLaunchKernelGGL(k_block_h, dim3((unsigned)std::min<int64_t>(nblk(t->nblk, 4), 65535)), dim3(256), 0, st,
                            t->frec, n, t->nblk, t->blkbox);
-    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(256), 0, st, counter, NGRP * CSTRIDE);
+    int* taken = ctx->d_counter + sph_ctx::CTR_PARK + CSTRIDE;
+    hipLaunchKernelGGL(k_zero_ctr, dim3(2), dim3(256), 0, st, counter, NGRP * CSTRIDE, taken);
     ev_mark(ctx, "ghost");
     ForceArgs a;
+    a.taken = taken;
     a.cells = t->cells;
     a.sets = t->d_sets;
     a.chunks = t->chunks;
@@ -1982,6 +2428,9 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     a.pv = t->pv;
     a.frec = t->frec;
     a.owned = t->owned;
+    a.active = nullptr;
+    a.list = t->order;
+    a.lcount = nullptr;
     a.mix = t->mix;
     a.csr = t->csr;
     a.csr_off = t->csr_off;
@@ -1995,6 +2444,8 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     a.plist = t->plist;
     a.npieces = (int)t->npieces;
     a.part = t->part;
+    a.park = (char*)t->b_park.p;
+    a.slots = (int)t->nslots;
     a.segidx = t->segidx;
     a.alpha = t->prm.alpha;
     a.ax = t->fax;
@@ -2007,10 +2458,22 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     a.hash = t->hashf;
     a.work = (unsigned long long*)(t->work_ctr + 256);
     a.rmax = rmax_of(t);
+    if (t->direct) {
+        launch_teams(ctx, t, a, t->nchunks, [&](auto W) {
+            constexpr int w = decltype(W)::value;
+            return t->hash ? k_force_teams<true, true, w> : k_force_teams<false, true, w>;
+        });
+        return;
+    }
     void (*kern)(ForceArgs);
     if (ext_kernels(t)) kern = t->hash ? k_force<true, true> : k_force<false, true>;
     else kern = t->hash ? k_force<true, false> : k_force<false, false>;
     hipLaunchKernelGGL(kern, dim3(persistent_blocks(ctx, t, t->nchunks, (const void*)kern)), dim3(BLK), 0, st, a);
+    if (t->nslots > 0)
+        launch_teams(ctx, t, a, t->nslots, [&](auto W) {
+            constexpr int w = decltype(W)::value;
+            return t->hash ? k_force_teams<true, false, w> : k_force_teams<false, false, w>;
+        });
     if (t->npieces > 0) {
         const dim3 gp(nblk(t->npieces, 4));
         if (t->hash) hipLaunchKernelGGL((k_force_pieces<true>), gp, dim3(256), 0, st, a);
@@ -2018,11 +2481,13 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     }
 }
 
-// A Newton step of every active particle.
+// A Newton step of every active particle (DENS_CTR: the density, force and
+// chunk-list counters).
+constexpr int DENS_CTR = 3 * NGRP * CSTRIDE;
 static void launch_newton(sph_ctx* ctx, sph_tree* t) {
-    hipLaunchKernelGGL(k_newton, dim3(nblk(t->n, 256)), dim3(256), 0, ctx->stream, t->n, t->d_sets, t->nsets,
-                       t->active, t->nw, t->dnw, t->ph, t->bound, t->lo, t->hi, t->dstep, (double)t->prm.n_target,
-                       (double)t->prm.h_tol, t->status);
+    hipLaunchKernelGGL(k_newton, dim3(nblk(t->n, 256)), dim3(256), 0, ctx->stream, t->n, ctx->d_counter, DENS_CTR,
+                       ctx->d_counter + sph_ctx::CTR_PARK, t->d_sets, t->nsets, t->active, t->nw, t->dnw, t->ph,
+                       t->bound, t->lo, t->hi, t->dstep, (double)t->prm.n_target, (double)t->prm.h_tol, t->status);
 }
 
 // status[1] and status[3+2s] = particles still active after the last Newton
@@ -2065,7 +2530,7 @@ static void zero_work(sph_ctx* ctx, sph_tree* t, int first, int words) {
 Err run_density(sph_ctx* ctx, sph_tree* t, const sph_density_out* out) {
     if (!t->built || !t->sorted) return Err{SPH_E_STATE, "density before build_cells/sort_pairs"};
     if (out && out->hash && !t->hash) return Err{SPH_E_ARG, "pair hash requested without SPH_FLAG_PAIR_HASH"};
-    ERRTRY(ensure_state(t));
+    ERRTRY(ensure_state(ctx, t));
     if (t->n == 0) return Err{};
     ev_mark(ctx, "start");
     zero_work(ctx, t, 0, 256);
@@ -2083,7 +2548,7 @@ Err run_solve(sph_ctx* ctx, sph_tree* t, const sph_density_out* out, int32_t* n_
     if (out && out->hash && !t->hash) return Err{SPH_E_ARG, "pair hash requested without SPH_FLAG_PAIR_HASH"};
     if (t->prm.max_iter < 1 || !(t->prm.h_tol > 0.f) || !(t->prm.n_target > 0.f))
         return Err{SPH_E_ARG, "bad solve parameters"};
-    ERRTRY(ensure_state(t));
+    ERRTRY(ensure_state(ctx, t));
     hipStream_t st = ctx->stream;
     const int64_t n = t->n;
     if (n_unconv) *n_unconv = 0;
@@ -2179,7 +2644,7 @@ Err run_solve(sph_ctx* ctx, sph_tree* t, const sph_density_out* out, int32_t* n_
 Err run_force(sph_ctx* ctx, sph_tree* t, const sph_force_out* out) {
     if (!t->have_density) return Err{SPH_E_STATE, "force before a density pass at the current h"};
     if (out && out->hash && !t->hash) return Err{SPH_E_ARG, "pair hash requested without SPH_FLAG_PAIR_HASH"};
-    ERRTRY(ensure_state(t));
+    ERRTRY(ensure_state(ctx, t));
     if (t->n == 0) return Err{};
     ev_mark(ctx, "start");
     zero_work(ctx, t, 256, 256);
@@ -2219,7 +2684,7 @@ Err set_halo(sph_ctx* ctx, sph_tree* t, const uint8_t* owned, const float* rho, 
         return Err{};
     }
     if (!rho || !drho) return Err{SPH_E_ARG, "halo densities missing"};
-    ERRTRY(ensure_state(t));
+    ERRTRY(ensure_state(ctx, t));
     void* p;
     ERRTRY(t->alloc(t->b_owned, (size_t)std::max<int64_t>(t->n, 1), &p));
     t->owned = (uint8_t*)p;
@@ -2256,7 +2721,7 @@ Err run_graph(sph_ctx* ctx, sph_tree* t, int k_iter, const sph_density_out* dout
     if (!n_unconv_dev) return Err{SPH_E_ARG, "null n_unconverged_dev"};
     if (((dout && dout->hash) || (fout && fout->hash)) && !t->hash)
         return Err{SPH_E_ARG, "pair hash requested without SPH_FLAG_PAIR_HASH"};
-    ERRTRY(ensure_state(t));
+    ERRTRY(ensure_state(ctx, t));
     if (t->n == 0) return Err{};
     std::vector<const void*> key;
     key.push_back((const void*)(intptr_t)k_iter);
@@ -2282,6 +2747,7 @@ Err run_graph(sph_ctx* ctx, sph_tree* t, int k_iter, const sph_density_out* dout
     val((uint64_t)t->ncells);
     val((uint64_t)t->nred);
     val((uint64_t)t->npieces);
+    val((uint64_t)t->nslots | (t->direct ? (uint64_t)1 << 32 : 0));
     // which kernels (with or without the heavy-chunk and cell-order code)
     // and which partners have sorted lists
     val((uint64_t)t->ext() | ((uint64_t)(uint32_t)t->max_sorted << 1));
@@ -2295,7 +2761,7 @@ Err run_graph(sph_ctx* ctx, sph_tree* t, int k_iter, const sph_density_out* dout
                           t->segpos, t->segidx, t->pos, t->plo, t->pv, t->ph, t->pu, t->bound, t->mix, t->iperm,
                           t->perm, t->owned, t->rho, t->hashd, t->lo, t->active, t->alist, t->status, t->frec,
                           t->hashf, t->partial, t->d_red, t->sums_int, t->part_cnt, t->blkbox, t->pcount,
-                          t->plist, t->part};
+                          t->plist, t->part, t->b_park.p, t->order};
     key.insert(key.end(), ptrs, ptrs + sizeof(ptrs) / sizeof(ptrs[0]));
     if (!t->gexec || key != t->gkey) {
         ++t->graph_captures;

@@ -18,6 +18,9 @@ constexpr int KEY_BITS_PER_DIM = 17;  // log2(top grid) + max depth must fit
 constexpr int SEG_LDS_MAX = 4096;     // largest (cell, axis) list sorted in LDS
 constexpr int CHUNK = 64;             // target particles per work item (one wave)
 constexpr int PIECE_MAX = 16;         // pieces a heavy chunk is split into at most
+constexpr int NGRP = 8;               // ranges of the chunk list, one per XCD
+constexpr int PARK_SLOTS = 2048;      // parked walks of a pass at most
+constexpr int PARK_BYTES = 4096;      // per parked walk
 constexpr int PART_WORDS = 8;         // partial sums of a particle in one piece (doubles)
 constexpr int SCAN_MIN = 256;         // swept records from which a partner may be read in cell order
 constexpr int SEG_LARGE_MAX = 16384;  // longest list sorted in LDS (longer: radix sort)
@@ -99,7 +102,7 @@ struct SetInfo {
     int32_t key_shift; // left shift that aligns this set's Morton code in the key
     int32_t depth;     // levels below the top grid the keys resolve for this set
     float drift;       // bound on any particle's displacement since the build (refreshes add up)
-    float pad_;
+    int32_t uneven;    // 1 if some cell is bisected or some top cell holds SCAN_MIN particles
 };
 
 // One cell of the hierarchy (all levels and sets in one table).  Cells of a
