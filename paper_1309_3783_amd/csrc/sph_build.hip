@@ -1141,195 +1141,230 @@ __global__ __launch_bounds__(256) void k_seg_sort_cell(int64_t nc, const SetInfo
     }
 }
 
-// Segments of 65..SEG_LDS_MAX entries (their (cell, axis) indices listed in
-// sel), sorted in LDS.  A block takes four lists at a time: each list of at
-// most WAVE_SORT_MAX entries is sorted by one wavefront on its own
-// (wave-level synchronisation only), the longer ones by the whole block.
-// Lists of up to BITONIC_MAX entries take a bitonic network in LDS; longer
-// ones a merge sort (runs of 16 sorted in registers, then merged pairwise
-// through LDS), which moves each key through LDS once per doubling instead
-// of once per bitonic stage.
-constexpr int WAVE_SORT_MAX = 1024;
-constexpr int BITONIC_MAX = 256;
-constexpr int MS_RUN = 16;
-static_assert(4 * WAVE_SORT_MAX <= SEG_LDS_MAX, "wave sorts share the block's array");
-static_assert(SEG_LDS_MAX <= 256 * MS_RUN, "the block's threads hold the whole list in runs");
-
-template <int NT>
-__device__ __forceinline__ void group_sync() {
-    if (NT == 64) wave_lds_sync();
-    else __syncthreads();
+// ---- sorts of whole lists on chip -----------------------------------------
+// A wave sorts 64 K keys in its registers (K per lane, lane l holds positions
+// [K l, K l + K)) with a bitonic network whose every comparison puts the
+// smaller key at the lower position: each merge of two sorted halves first
+// compares position i with its mirror image in the pair of halves, then at
+// distances of a quarter, an eighth ... of the pair.  Keys of other lanes come
+// by data-parallel moves within a row of 16 lanes and by cross-lane swizzles
+// beyond, so that no key goes through LDS: a merge sort in LDS from runs of 16
+// keys per thread spent two thirds of its LDS cycles on bank conflicts and left
+// half of the lanes idle on lists of 512 (all lists of 65..4096 entries of a
+// clumpy set of 8*10^6: 3.31 ms then, 1.82 now; of 10^6: 0.52, now 0.25).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
 }
-
-template <int NT>
-__device__ __forceinline__ void bitonic_lds(uint64_t* s, int P, int t) {
-    for (int size = 2; size <= P; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int e = t; e < P / 2; e += NT) {
-                const int i = 2 * e - (e & (stride - 1));
-                const int j = i + stride;
-                const bool up = ((i & size) == 0);
-                const uint64_t a = s[i], b = s[j];
-                if ((a > b) == up) {
-                    s[i] = b;
-                    s[j] = a;
-                }
-            }
-            group_sync<NT>();
-        }
-    }
+// the value of lane ^ X (X a power of two, or one less)
+template <int X>
+__device__ __forceinline__ uint32_t from_lane_xor(uint32_t v) {
+    if (X == 1) return dpp<0xB1>(v);          // quad_perm 1 0 3 2
+    if (X == 2) return dpp<0x4E>(v);          // quad_perm 2 3 0 1
+    if (X == 3) return dpp<0x1B>(v);          // quad_perm 3 2 1 0
+    if (X == 7) return dpp<0x141>(v);         // row_half_mirror
+    if (X == 8) return dpp<0x128>(v);         // row_ror:8
+    if (X == 15) return dpp<0x140>(v);        // row_mirror
+    if (X < 32) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (X << 10) | 0x1F);
+    return (uint32_t)__shfl_xor((int)v, X, 64);
 }
-
+template <int X>
+__device__ __forceinline__ uint64_t from_lane_xor(uint64_t v) {
+    return (uint64_t)from_lane_xor<X>((uint32_t)v) | (uint64_t)from_lane_xor<X>((uint32_t)(v >> 32)) << 32;
+}
 __device__ __forceinline__ void cmp_swap(uint64_t& x, uint64_t& y) {
     const uint64_t a = x, b = y;
     const bool sw = b < a;
     x = sw ? b : a;
     y = sw ? a : b;
 }
-
-// ascending sort of 16 keys held in registers (bitonic network, fixed indices)
-__device__ __forceinline__ void sort_run(uint64_t (&r)[MS_RUN]) {
+// one step against the lanes at lane ^ X, register k against k ^ KX
+template <int K, int X, int KX>
+__device__ __forceinline__ void lane_step(uint64_t (&r)[K], int lane) {
+    constexpr int top = (X + 1) & X ? X : (X + 1) / 2;   // the highest bit of X: set in the upper of two lanes
+    const bool upper = (lane & top) != 0;
 #pragma unroll
-    for (int lg = 1; lg <= 4; ++lg) {
-#pragma unroll
-        for (int ls = lg - 1; ls >= 0; --ls) {
-#pragma unroll
-            for (int i = 0; i < MS_RUN; ++i) {
-                const int j = i ^ (1 << ls);
-                if (j > i) {
-                    if ((i & (1 << lg)) == 0) cmp_swap(r[i], r[j]);
-                    else cmp_swap(r[j], r[i]);
-                }
-            }
-        }
+    for (int k = 0; k < K; ++k) {
+        if (KX != 0 && (k ^ KX) < k) continue;
+        // (a few keys in flight: all of them at once would not fit)
+        if (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        uint64_t o0 = from_lane_xor<X>(r[k ^ KX]), o1 = 0;
+        if (KX != 0) o1 = from_lane_xor<X>(r[k]);
+        r[k] = ((o0 < r[k]) != upper) ? o0 : r[k];
+        if (KX != 0) r[k ^ KX] = ((o1 < r[k ^ KX]) != upper) ? o1 : r[k ^ KX];
     }
 }
-
-// Merge sort of the P keys in s (P a power of two, 2 * MS_RUN <= P <=
-// NT * MS_RUN) by the NT threads of a wave (NT = 64) or block (NT = 256);
-// thread t owns output positions [16 t, 16 t + 16).  Each round merges
-// pairs of sorted runs of length L: a thread finds where its 16 outputs
-// start on the merge path of its pair (binary search), merges them into
-// registers, and all write back after a barrier.  Keys are compared as
-// unsigned integers; equal keys (the padding) take the first run first.
-template <int NT>
-__device__ __forceinline__ void merge_sort_lds(uint64_t* s, int P, int t) {
-    const bool on = t * MS_RUN < P;
-    uint64_t r[MS_RUN];
-    if (on) {
+// the steps at distances D, D/2 ... 1 (positions)
+template <int K, int D>
+__device__ __forceinline__ void half_clean(uint64_t (&r)[K], int lane) {
+    if constexpr (D >= K) {
+        lane_step<K, D / K, 0>(r, lane);
+    } else {
 #pragma unroll
-        for (int k = 0; k < MS_RUN; ++k) r[k] = s[t * MS_RUN + k];
-        sort_run(r);
-#pragma unroll
-        for (int k = 0; k < MS_RUN; ++k) s[t * MS_RUN + k] = r[k];
+        for (int k = 0; k < K; ++k)
+            if ((k & D) == 0) cmp_swap(r[k], r[k ^ D]);
     }
-    group_sync<NT>();
-    for (int L = MS_RUN; L < P; L <<= 1) {
-        if (on) {
-            const int d = (t * MS_RUN) & (2 * L - 1);   // position in the merged pair
-            const uint64_t* A = s + (t * MS_RUN - d);
-            const uint64_t* B = A + L;
-            int lo = d > L ? d - L : 0, hi = d < L ? d : L;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (!(B[d - 1 - mid] < A[mid])) lo = mid + 1;
-                else hi = mid;
-            }
-            int i = lo, j = d - lo;
-            uint64_t a = i < L ? A[i] : 0ull, b = j < L ? B[j] : 0ull;
-            // one LDS read per output: the successor of the key taken
+    if constexpr (D > 1) half_clean<K, D / 2>(r, lane);
+}
+template <int K, int S>
+__device__ __forceinline__ void wave_sort(uint64_t (&r)[K], int lane) {
+    if constexpr (S > 2) wave_sort<K, S / 2>(r, lane);
+    if constexpr (S <= K) {
 #pragma unroll
-            for (int k = 0; k < MS_RUN; ++k) {
-                const bool ta = i < L && (j >= L || !(b < a));
-                r[k] = ta ? a : b;
-                i += ta ? 1 : 0;
-                j += ta ? 0 : 1;
-                const int q = ta ? i : j;
-                const uint64_t v = q < L ? (ta ? A : B)[q] : 0ull;
-                a = ta ? v : a;
-                b = ta ? b : v;
-            }
-        }
-        group_sync<NT>();
-        if (on) {
-#pragma unroll
-            for (int k = 0; k < MS_RUN; ++k) s[t * MS_RUN + k] = r[k];
-        }
-        group_sync<NT>();
+        for (int k = 0; k < K; ++k)
+            if ((k & (S / 2)) == 0) cmp_swap(r[k], r[k ^ (S - 1)]);
+    } else {
+        lane_step<K, S / K - 1, K - 1>(r, lane);
     }
+    if constexpr (S > 2) half_clean<K, S / 4 < 1 ? 1 : S / 4>(r, lane);
 }
 
-__global__ __launch_bounds__(256) void k_seg_sort_lds(const uint32_t* __restrict__ sel, int64_t nsel,
-                                                      const uint32_t* __restrict__ off, const SetInfo* sets,
-                                                      const Cell* __restrict__ cells,
-                                                      const float4* __restrict__ pos, const float* __restrict__ ph,
-                                                      float4* __restrict__ sproj, uint32_t* __restrict__ sidx) {
-    __shared__ uint64_t s[SEG_LDS_MAX];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int64_t g0 = (int64_t)blockIdx.x * 4; g0 < nsel; g0 += (int64_t)gridDim.x * 4) {
-        // short lists: one per wave
-        if (g0 + w < nsel) {
-            const uint32_t ca = sel[g0 + w];
-            const Cell C = cells[ca / NAXES];
-            const int ax = (int)(ca % NAXES);
-            const int n = __builtin_amdgcn_readfirstlane(C.count);
-            if (n > 64 && n <= WAVE_SORT_MAX) {
-                uint64_t* sw = s + w * WAVE_SORT_MAX;
-                int P = 1;
-                while (P < n) P <<= 1;
-                const float lim = small_h_limit(sets, C);
-                for (int e = lane; e < P; e += 64) {
-                    uint64_t k = ~0ull;
-                    if (e < n) k = seg_key(project(pos[C.first + e], ax), ph[C.first + e] > lim ? 1 : 0, (uint32_t)e);
-                    sw[e] = k;
-                }
-                wave_lds_sync();
-                if (P <= BITONIC_MAX) bitonic_lds<64>(sw, P, lane);
-                else merge_sort_lds<64>(sw, P, lane);
-                const uint32_t o = off[ca];
-                for (int e = lane; e < n; e += 64) {
-                    const uint64_t k = sw[e];
-                    const uint32_t j = (uint32_t)C.first + (uint32_t)(k & 0xFFFFFFFFu);
-                    sproj[o + e] = pos[j];
-                    sidx[o + e] = j;
-                }
-            }
+// The n (<= 64 K) entries of cell C's list along axis ax, sorted by one wave
+// and written from o on.  si: room for 64 K indices in LDS, through which
+// the sorted order passes so that the entries leave in rows.
+template <int K>
+__device__ __forceinline__ void wave_list(const Cell& C, int ax, int n, float lim, uint32_t o, uint32_t* si,
+                                          const float4* __restrict__ pos, const float* __restrict__ ph,
+                                          float4* __restrict__ sproj, uint32_t* __restrict__ sidx) {
+    const int lane = threadIdx.x & 63;
+    uint64_t r[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int e = 64 * k + lane;
+        if (k % 4 == 0) asm volatile("" ::: "memory");   // (four positions in flight, not sixteen)
+        r[k] = e < n ? seg_key(project(pos[C.first + e], ax), ph[C.first + e] > lim ? 1 : 0, (uint32_t)e) : ~0ull;
+    }
+    wave_sort<K, 64 * K>(r, lane);
+#pragma unroll
+    for (int k = 0; k < K; ++k) si[K * lane + k] = (uint32_t)r[k];
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int e = 64 * k + lane;
+        if (k % 4 == 0) asm volatile("" ::: "memory");
+        if (e < n) {
+            const uint32_t j = (uint32_t)C.first + si[e];
+            sproj[o + e] = pos[j];
+            sidx[o + e] = j;
+        }
+    }
+    wave_lds_sync();
+}
+
+// The same by a block of NT threads for up to NT K entries: each wave sorts
+// 64 K keys, then pairs of sorted runs are merged through s (NT K keys), a
+// thread finding where its K outputs start on the merge path of its pair
+// (binary search).  Keys are placed so that threads reading their runs of K,
+// or rows, spread over the banks.
+__device__ __forceinline__ int bank_place(int i) { return i ^ ((i >> 4) & 15); }
+template <int NT, int K>
+__device__ __forceinline__ void block_list(const Cell& C, int ax, int n, float lim, uint32_t o, uint64_t* s,
+                                           const float4* __restrict__ pos, const float* __restrict__ ph,
+                                           float4* __restrict__ sproj, uint32_t* __restrict__ sidx) {
+    const int t = threadIdx.x;
+    uint64_t r[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int e = NT * k + t;
+        if (k % 4 == 0) asm volatile("" ::: "memory");
+        r[k] = e < n ? seg_key(project(pos[C.first + e], ax), ph[C.first + e] > lim ? 1 : 0, (uint32_t)e) : ~0ull;
+    }
+    wave_sort<K, 64 * K>(r, t & 63);
+#pragma unroll
+    for (int k = 0; k < K; ++k) s[bank_place(K * t + k)] = r[k];
+    __syncthreads();
+#pragma unroll 1
+    for (int L = 64 * K; L < NT * K; L <<= 1) {
+        const int d = (t * K) & (2 * L - 1);   // position in the merged pair
+        const int A = t * K - d, B = A + L;
+        int lo = d > L ? d - L : 0, hi = d < L ? d : L;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (!(s[bank_place(B + d - 1 - mid)] < s[bank_place(A + mid)])) lo = mid + 1;
+            else hi = mid;
+        }
+        int i = A + lo, j = B + d - lo;
+        uint64_t a = i < B ? s[bank_place(i)] : ~0ull, b = j < B + L ? s[bank_place(j)] : ~0ull;
+        // one LDS read per output: the successor of the key taken (past the
+        // end of a run the largest key stands, as in the padding)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool ta = !(b < a);
+            r[k] = ta ? a : b;
+            i += ta ? 1 : 0;
+            j += ta ? 0 : 1;
+            const int q = ta ? i : j;
+            const uint64_t v = q < (ta ? B : B + L) ? s[bank_place(q)] : ~0ull;
+            a = ta ? v : a;
+            b = ta ? b : v;
         }
         __syncthreads();
-        // longer lists: the whole block, one after the other
-        for (int k4 = 0; k4 < 4 && g0 + k4 < nsel; ++k4) {
-            const uint32_t ca = sel[g0 + k4];
-            const Cell C = cells[ca / NAXES];
-            const int ax = (int)(ca % NAXES);
-            const int n = C.count;
-            if (n <= WAVE_SORT_MAX || n > SEG_LDS_MAX) continue;
-            int P = 1;
-            while (P < n) P <<= 1;
-            const float lim = small_h_limit(sets, C);
-            for (int e = threadIdx.x; e < P; e += blockDim.x) {
-                uint64_t k = ~0ull;
-                if (e < n) k = seg_key(project(pos[C.first + e], ax), ph[C.first + e] > lim ? 1 : 0, (uint32_t)e);
-                s[e] = k;
-            }
-            __syncthreads();
-            merge_sort_lds<256>(s, P, threadIdx.x);
-            const uint32_t o = off[ca];
-            for (int e = threadIdx.x; e < n; e += blockDim.x) {
-                const uint64_t k = s[e];
-                const uint32_t j = (uint32_t)C.first + (uint32_t)(k & 0xFFFFFFFFu);
-                sproj[o + e] = pos[j];
-                sidx[o + e] = j;
-            }
-            __syncthreads();
-        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) s[bank_place(K * t + k)] = r[k];
+        __syncthreads();
+    }
+#pragma unroll 1
+    for (int e = t; e < n; e += NT) {
+        const uint32_t j = (uint32_t)C.first + (uint32_t)s[bank_place(e)];
+        sproj[o + e] = pos[j];
+        sidx[o + e] = j;
+    }
+    __syncthreads();
+}
+
+// Segments of 65..SEG_LDS_MAX entries (their (cell, axis) indices listed in
+// sel): those of at most WAVE_SORT_MAX entries sorted by one wave each
+// (69 registers: sixteen keys per lane would leave room for half the waves),
+// the longer ones by a block each, in two kernels.
+constexpr int WAVE_SORT_MAX = 512;
+static_assert(SEG_LDS_MAX == 256 * 16, "the block's threads hold the whole list");
+
+__global__ __launch_bounds__(256) void k_seg_sort_wave(const uint32_t* __restrict__ sel, int64_t nsel,
+                                                       const uint32_t* __restrict__ off, const SetInfo* sets,
+                                                       const Cell* __restrict__ cells,
+                                                       const float4* __restrict__ pos, const float* __restrict__ ph,
+                                                       float4* __restrict__ sproj, uint32_t* __restrict__ sidx) {
+    __shared__ uint32_t s[4 * WAVE_SORT_MAX];
+    const int w = threadIdx.x >> 6;
+    uint32_t* si = s + w * WAVE_SORT_MAX;
+    for (int64_t g = (int64_t)blockIdx.x * 4 + w; g < nsel; g += (int64_t)gridDim.x * 4) {
+        const uint32_t ca = sel[g];
+        const Cell C = cells[ca / NAXES];
+        const int ax = (int)(ca % NAXES);
+        const int n = __builtin_amdgcn_readfirstlane(C.count);
+        if (n <= 64 || n > WAVE_SORT_MAX) continue;
+        const float lim = small_h_limit(sets, C);
+        const uint32_t o = off[ca];
+        if (n <= 128) wave_list<2>(C, ax, n, lim, o, si, pos, ph, sproj, sidx);
+        else if (n <= 256) wave_list<4>(C, ax, n, lim, o, si, pos, ph, sproj, sidx);
+        else wave_list<8>(C, ax, n, lim, o, si, pos, ph, sproj, sidx);
+    }
+}
+
+__global__ __launch_bounds__(256, 4) void k_seg_sort_lds(const uint32_t* __restrict__ sel, int64_t nsel,
+                                                         const uint32_t* __restrict__ off, const SetInfo* sets,
+                                                         const Cell* __restrict__ cells,
+                                                         const float4* __restrict__ pos, const float* __restrict__ ph,
+                                                         float4* __restrict__ sproj, uint32_t* __restrict__ sidx) {
+    __shared__ uint64_t s[SEG_LDS_MAX];
+    for (int64_t g = blockIdx.x; g < nsel; g += gridDim.x) {
+        const uint32_t ca = sel[g];
+        const Cell C = cells[ca / NAXES];
+        const int ax = (int)(ca % NAXES);
+        const int n = C.count;
+        if (n <= WAVE_SORT_MAX || n > SEG_LDS_MAX) continue;
+        const float lim = small_h_limit(sets, C);
+        if (n <= 1024) block_list<256, 4>(C, ax, n, lim, off[ca], s, pos, ph, sproj, sidx);
+        else if (n <= 2048) block_list<256, 8>(C, ax, n, lim, off[ca], s, pos, ph, sproj, sidx);
+        else block_list<256, 16>(C, ax, n, lim, off[ca], s, pos, ph, sproj, sidx);
     }
 }
 
 // Lists of SEG_LDS_MAX+1 .. SEG_LARGE_MAX entries (the long class, listed in
-// big): one block of LARGE_BS threads per list, the merge sort in 128 KB of
-// LDS.  Longer lists are left to the global radix sort.
+// big): one block of LARGE_BS threads per list, merged in 128 KB of LDS.
+// Longer lists are left to the global radix sort.
 constexpr int LARGE_BS = 1024;
-static_assert(SEG_LARGE_MAX <= LARGE_BS * MS_RUN, "the block's threads hold the whole list in runs");
+static_assert(SEG_LARGE_MAX == LARGE_BS * 16, "the block's threads hold the whole list");
 __global__ __launch_bounds__(LARGE_BS) void k_seg_sort_large(const uint32_t* __restrict__ big,
                                                              const uint32_t* __restrict__ off, const SetInfo* sets,
                                                              const Cell* __restrict__ cells,
@@ -1342,23 +1377,9 @@ __global__ __launch_bounds__(LARGE_BS) void k_seg_sort_large(const uint32_t* __r
     const int n = C.count;
     if (n <= SEG_LDS_MAX || n > SEG_LARGE_MAX) return;
     const int ax = (int)(ca % NAXES);
-    int P = 1;
-    while (P < n) P <<= 1;
     const float lim = small_h_limit(sets, C);
-    for (int e = threadIdx.x; e < P; e += LARGE_BS) {
-        uint64_t k = ~0ull;
-        if (e < n) k = seg_key(project(pos[C.first + e], ax), ph[C.first + e] > lim ? 1 : 0, (uint32_t)e);
-        s[e] = k;
-    }
-    __syncthreads();
-    merge_sort_lds<LARGE_BS>(s, P, threadIdx.x);
-    const uint32_t o = off[ca];
-    for (int e = threadIdx.x; e < n; e += LARGE_BS) {
-        const uint64_t k = s[e];
-        const uint32_t j = (uint32_t)C.first + (uint32_t)(k & 0xFFFFFFFFu);
-        sproj[o + e] = pos[j];
-        sidx[o + e] = j;
-    }
+    if (n <= 8 * LARGE_BS) block_list<LARGE_BS, 8>(C, ax, n, lim, off[ca], s, pos, ph, sproj, sidx);
+    else block_list<LARGE_BS, 16>(C, ax, n, lim, off[ca], s, pos, ph, sproj, sidx);
 }
 
 __global__ __launch_bounds__(256) void k_big_keys(const uint32_t* __restrict__ big,
@@ -2024,7 +2045,10 @@ Err sort_pairs(sph_ctx* ctx, sph_tree* t) {
         HIPTRY(hipGetLastError());
     }
     if (nmid > 0) {
-        hipLaunchKernelGGL(k_seg_sort_lds, dim3((unsigned)std::min<uint32_t>((nmid + 3) / 4, 65535)), dim3(256), 0, st, mids,
+        hipLaunchKernelGGL(k_seg_sort_wave, dim3((unsigned)std::min<uint32_t>((nmid + 3) / 4, 65535)), dim3(256), 0,
+                           st, mids, (int64_t)nmid, t->segoff, t->d_sets, t->cells, t->pos, t->ph, t->segpos,
+                           t->segidx);
+        hipLaunchKernelGGL(k_seg_sort_lds, dim3((unsigned)std::min<uint32_t>(nmid, 65535)), dim3(256), 0, st, mids,
                            (int64_t)nmid, t->segoff, t->d_sets, t->cells, t->pos, t->ph, t->segpos, t->segidx);
         HIPTRY(hipGetLastError());
     }
