@@ -2342,18 +2342,21 @@ static DensArgs dens_args(sph_tree* t, int* counter, const int* lcount) {
     return a;
 }
 
-// A team kernel over items chunks or parked walks: a block per item, at most
-// as many as fit at once.  Eight waves a block where that leaves blocks idle
-// otherwise (30011 particles, 597 chunks: 1.05 ms for the whole pass over
-// density and force against 1.12 with four and 1.15 with sixteen), four
-// where the chunks are more than fit (200000 particles, 4819 chunks: 5.0
-// against 5.6 ms).
+// A team kernel over items chunks or parked walks.  Chunks: a block each, so
+// that the next one starts wherever a block ends (200000 particles, 4819
+// chunks, blocks of four waves: the h solve and force 4.2 ms with the four
+// blocks per CU that fit at once taking them in turn, 3.5 with a block each).
+// Parked walks, of which most passes have few: two blocks per CU take them
+// in turn.  Eight waves a block where that leaves blocks idle otherwise (30011
+// particles, 597 chunks: 1.05 ms for the whole pass over density and force
+// against 1.12 with four and 1.15 with sixteen), four where the chunks are
+// more than fit (200000 particles: 3.5 against 4.2 ms with two).
 template <class A, class F>
 static void launch_teams(const sph_ctx* ctx, const sph_tree* t, const A& a, int64_t items, F kern) {
     const bool wide = items <= 4 * (int64_t)ctx->n_cu || !t->direct;
-    int bpc = wide ? 2 : 4;
-    if (t->prm.blocks_per_cu > 0) bpc = std::min(bpc, t->prm.blocks_per_cu);
-    const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(items, (int64_t)ctx->n_cu * bpc)));
+    int64_t blocks = t->direct ? items : std::min<int64_t>(items, 2 * (int64_t)ctx->n_cu);
+    if (t->prm.blocks_per_cu > 0) blocks = std::min<int64_t>(blocks, (int64_t)ctx->n_cu * t->prm.blocks_per_cu);
+    const dim3 grid((unsigned)std::max<int64_t>(1, blocks));
     if (wide) hipLaunchKernelGGL(kern(std::integral_constant<int, 8>{}), grid, dim3(512), 0, ctx->stream, a);
     else hipLaunchKernelGGL(kern(std::integral_constant<int, 4>{}), grid, dim3(256), 0, ctx->stream, a);
 }
