@@ -57,6 +57,15 @@ __device__ __forceinline__ uint64_t uni64(uint64_t v) {
 __device__ __forceinline__ int bits_below(uint64_t m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
+// The larger of two numbers (neither a signalling NaN: fmaxf quiets its
+// arguments first, an instruction each time), and a number limited to [0, 1]
+// (a modifier of the instruction that made it).
+__device__ __forceinline__ float vmax(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float clamp01(float v) { return __builtin_amdgcn_fmed3f(v, 0.f, 1.f); }
 // Hardware square root and reciprocal (1 ulp): the arguments here are
 // normal numbers (r^2 >= 2^-48 for distinct particles), and 1-ulp results
 // are far inside the stated tolerances.
@@ -1325,7 +1334,7 @@ struct DensP {
     template <int W>
     struct Lds {
         float4 p[TILE * W];     // x, y, z (shifted into the target's frame), m
-        uint64_t m[TILE * W];   // pair-hash terms
+        uint64_t m[HASH ? TILE * W : 1];   // pair-hash terms
         int n[TILE * W];        // counts of a tile (put)
     };
     // a lane's sums and counts of one tile, to LDS and added from there
@@ -1400,7 +1409,7 @@ struct DensP {
         const float u = r * L.hinv;
         // the two pieces of the cubic spline without a branch:
         // f = 2 (1-u)^3 - 8 max(0, 1/2-u)^3,  f' = -6 (1-u)^2 + 24 max(0, 1/2-u)^2
-        const float t1 = 1.f - u, s1 = fmaxf(0.5f - u, 0.f);
+        const float t1 = 1.f - u, s1 = clamp01(0.5f - u);
         const float t2 = t1 * t1, s2 = s1 * s1;
         const float f = fmaf(2.f * t2, t1, -8.f * s2 * s1);
         const float df = fmaf(24.f, s2, -6.f * t2);
@@ -1544,9 +1553,11 @@ struct ForceArgs {
 
 __device__ __forceinline__ float gradF(float q, float h, float rinv) {
     // f'(q)/q of the cubic spline, zero outside the support
-    float t = 1.f - q;
-    float outer = q < 1.f ? -6.f * t * t * h * rinv : 0.f;
-    return q < 0.5f ? fmaf(18.f, q, -12.f) : outer;
+    float t = clamp01(1.f - q);
+    float outer = -6.f * t * t * h * rinv;
+    float inner = fmaf(18.f, q, -12.f);
+    asm("" : "+v"(inner), "+v"(outer));   // (a select, not two branches)
+    return q < 0.5f ? inner : outer;
 }
 
 template <bool HASH>
@@ -1583,18 +1594,23 @@ struct ForceP {
     }
     template <int W>
     struct Lds {
-        float4 p[TILE * W];    // x, y, z (shifted into the target's frame), h
+        float4 p[TILE * W];    // x, y, z (shifted into the target's frame), h^2
         float4 h[TILE * W];    // m, 1/h, K = 8/(pi h^5), A
         float4 v[TILE * W];    // vx, vy, vz, rho
-        float c[TILE * W];     // sound speed
-        uint64_t m[TILE * W];  // pair-hash terms
+        float4 c[TILE * W];    // sound speed, h, pair-hash term (all arrays of one stride: one address per pair)
     };
+    static __device__ __forceinline__ float4 hash_words(float x, float y, uint64_t m) {
+        return make_float4(x, y, __uint_as_float((uint32_t)m), __uint_as_float((uint32_t)(m >> 32)));
+    }
+    static __device__ __forceinline__ uint64_t hash_of(const float4& v) {
+        return (uint64_t)__float_as_uint(v.z) | (uint64_t)__float_as_uint(v.w) << 32;
+    }
     // a lane's sums and counts of one tile, to LDS and added from there
     template <int W>
     static __device__ __forceinline__ void put(Lds<W>& S, int at, const Acc& A) {
         S.p[at] = make_float4(A.ax, A.ay, A.az, A.du);
         S.h[at] = make_float4(A.S, A.vs, __int_as_float(A.nn), 0.f);
-        if (HASH) S.m[at] = A.hs;
+        if (HASH) S.v[at] = hash_words(0.f, 0.f, A.hs);
     }
     template <int W>
     static __device__ __forceinline__ void get(const Lds<W>& S, int at, Acc& A) {
@@ -1606,7 +1622,7 @@ struct ForceP {
         A.S = u.x;
         A.vs = fmaxf(A.vs, u.y);
         A.nn += __float_as_int(u.z);
-        if (HASH) A.hs += S.m[at];
+        if (HASH) A.hs += hash_of(S.v[at]);
     }
     // the sums of a parked walk (at tile boundaries), a lane's every 64th
     static __device__ __forceinline__ void save(const Acc& A, double* q) {
@@ -1688,7 +1704,7 @@ struct ForceP {
     }
     static __device__ __forceinline__ float cut(float hmax, float hpart) { return fmaxf(hmax, hpart); }
     // squared cutoff of a pair: max(h_i, h_j)
-    static __device__ __forceinline__ float lim2(float hi2, float hj) { return fmaxf(hi2, hj * hj); }
+    static __device__ __forceinline__ float lim2(float hi2, float hj2) { return vmax(hi2, hj2); }
     // where a part's largest h reaches well beyond the chunk's own cutoff,
     // the partner's force record is read before the record is filtered: its
     // own h bounds its reach (the cutoff is max(h_i, h_j))
@@ -1715,18 +1731,18 @@ struct ForceP {
                                                  float Sz, const Args& a, const Pre& pr, bool loaded, bool uselo) {
         const float4 fj = loaded ? pr.f : a.frec[j];
         const float4 lo = uselo ? a.plo[j] : make_float4(0.f, 0.f, 0.f, 0.f);
-        S.p[slot] = make_float4((pj.x + Sx) + lo.x, (pj.y + Sy) + lo.y, (pj.z + Sz) + lo.z, fj.x);
+        S.p[slot] = make_float4((pj.x + Sx) + lo.x, (pj.y + Sy) + lo.y, (pj.z + Sz) + lo.z, fj.x * fj.x);
         S.h[slot] = make_float4(pj.w, frcp(fj.x), fj.w, fj.y);
         S.v[slot] = a.pv[j];
-        S.c[slot] = fj.z;
-        if (HASH) S.m[slot] = a.mix[j];
+        if (HASH) S.c[slot] = hash_words(fj.z, fj.x, a.mix[j]);
+        else *(float2*)&S.c[slot] = make_float2(fj.z, fj.x);
     }
     template <int W>
     static __device__ __forceinline__ void pair(Acc& A, const Lds<W>& S, int j, const Lane& L) {
         const float4 q = S.p[j];
         const float4 sh = S.h[j];
         const float4 sv = S.v[j];
-        const float cj = S.c[j];
+        const float2 ch = *(const float2*)&S.c[j];
         const float dx = L.x.x - q.x, dy = L.x.y - q.y, dz = L.x.z - q.z;
         // 1/r from one reciprocal square root, r = r^2 / r; two distinct
         // particles at one FP32 point (closer than a rounding of their
@@ -1735,13 +1751,13 @@ struct ForceP {
         const float rinv = r2 > 0.f ? frsq(r2) : 0.f;
         const float r = r2 * rinv;
         const float ki = L.K * gradF(r * L.hinv, L.h, rinv);
-        const float kj = sh.z * gradF(r * sh.y, q.w, rinv);
+        const float kj = sh.z * gradF(r * sh.y, ch.y, rinv);
         const float vdx = L.v.x - sv.x, vdy = L.v.y - sv.y, vdz = L.v.z - sv.z;
         const float vdotx = fmaf(vdx, dx, fmaf(vdy, dy, vdz * dz));
         // approaching pairs only (w < 0): with w clamped at 0 the term
         // vanishes exactly, without a branch
         const float wn = fminf(vdotx * rinv, 0.f);
-        const float vsig = fmaf(-3.f, wn, L.c + cj);
+        const float vsig = fmaf(-3.f, wn, L.c + ch.x);
         const float visc = -L.alpha * vsig * wn * frcp(L.v.w + sv.w);
         const float kbar = 0.5f * (ki + kj);
         const float s = fmaf(L.A, ki, fmaf(sh.w, kj, visc * kbar));
@@ -1751,9 +1767,9 @@ struct ForceP {
         A.ay = fmaf(-ms, dy, A.ay);
         A.az = fmaf(-ms, dz, A.az);
         A.du = fmaf(mj * vdotx, fmaf(L.A, ki, 0.5f * visc * kbar), A.du);
-        A.vs = fmaxf(A.vs, vsig);
+        A.vs = vmax(A.vs, vsig);
         A.S = fmaf(fabsf(ms), r, A.S);
-        if (HASH) A.hs += S.m[j];
+        if (HASH) A.hs += hash_of(S.c[j]);
     }
 };
 
