@@ -268,11 +268,13 @@ __global__ void k_top_cells(const SetInfo* sets, int nsets, int ntop, int bmax,
 
 // One wave per cell of level `level`: particle range (children of a split
 // parent look theirs up inside the parent's range), max decision h, the
-// number with h < edge/2, and the split decision.
+// number with h < edge/2, and the split decision (also
+// to flags, from the level's first cell on).
 __global__ __launch_bounds__(256) void k_cell_stats(SetInfo* sets, int bmax, int level,
                                                     int64_t c0, int64_t c1, const uint64_t* __restrict__ key,
                                                     const float* __restrict__ hdec, int n_split,
-                                                    float split_frac, Cell* __restrict__ cells) {
+                                                    float split_frac, Cell* __restrict__ cells,
+                                                    uint32_t* __restrict__ flags) {
     const int lane = threadIdx.x & 63;
     int64_t c = c0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (c >= c1) return;
@@ -303,14 +305,10 @@ __global__ __launch_bounds__(256) void k_cell_stats(SetInfo* sets, int bmax, int
         C.split = (level < S.depth && C.count > n_split &&
                    (double)nsmall > (double)split_frac * (double)C.count) ? 1u : 0u;
         cells[c] = C;
+        flags[c - c0] = C.split;
         // (every writer writes the same value)
         if (C.split || (level == 0 && C.count >= SCAN_MIN)) sets[C.set].uneven = 1;
     }
-}
-
-__global__ void k_split_flags(const Cell* __restrict__ cells, int64_t c0, int64_t c1, uint32_t* flags) {
-    int64_t c = c0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < c1) flags[c - c0] = cells[c].split;
 }
 
 __global__ void k_make_children(int64_t c0, int64_t c1, int64_t next0, const uint32_t* __restrict__ sidx,
@@ -547,7 +545,11 @@ __global__ void k_task_emit(const int4* __restrict__ tasks, int64_t nt, const Ce
 // Leaves -> work chunks of at most CHUNK particles; per-particle h bound.
 // ---------------------------------------------------------------------------
 // The number of non-empty leaves and the largest leaf (one atomic per block).
-__global__ __launch_bounds__(256) void k_chunk_count(const Cell* __restrict__ cells, int64_t nc, int* stats) {
+// The chunks are numbered in particle (cell) order, so that the chunk list
+// runs through space in Morton order: a leaf marks the first particle of each
+// of its chunks, a scan of the marks gives the chunk numbers.
+__global__ __launch_bounds__(256) void k_chunk_count(const Cell* __restrict__ cells, int64_t nc, int* stats,
+                                                     uint32_t* __restrict__ mark) {
     int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool leaf = false;
     int count = 0;
@@ -555,6 +557,7 @@ __global__ __launch_bounds__(256) void k_chunk_count(const Cell* __restrict__ ce
         const Cell C = cells[c];
         leaf = !C.split && C.count > 0;
         count = leaf ? C.count : 0;
+        for (int s = 0; s < count; s += CHUNK) mark[C.first + s] = 1u;
     }
     int nl = __popcll(__ballot(leaf));
     for (int d = 32; d >= 1; d >>= 1) count = max(count, __shfl_xor(count, d, 64));
@@ -572,17 +575,6 @@ __global__ __launch_bounds__(256) void k_chunk_count(const Cell* __restrict__ ce
             atomicMax(&stats[1], count);
         }
     }
-}
-
-// The chunks are numbered in particle (cell) order, so that the chunk list
-// runs through space in Morton order: a leaf marks the first particle of each
-// of its chunks, a scan of the marks gives the chunk numbers.
-__global__ void k_chunk_mark(const Cell* __restrict__ cells, int64_t nc, uint32_t* __restrict__ mark) {
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nc) return;
-    const Cell C = cells[c];
-    if (C.split || C.count == 0) return;
-    for (int s = 0; s < C.count; s += CHUNK) mark[C.first + s] = 1u;
 }
 
 __global__ void k_chunk_emit(const Cell* __restrict__ cells, int64_t nc, const uint32_t* __restrict__ num,
@@ -1012,10 +1004,6 @@ __global__ __launch_bounds__(256) void k_seg_lens(const uint32_t* __restrict__ n
         v = s_v[0] + s_v[1] + s_v[2] + s_v[3];
         if (v) atomicAdd(total64, v);
     }
-}
-
-__global__ void k_copy_u32(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, int n) {
-    if ((int)threadIdx.x < n) dst[threadIdx.x] = src[threadIdx.x];
 }
 
 // After the scans: lists nobody needs get offset ~0; the mid-size and long
@@ -1520,8 +1508,9 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
     std::vector<float> hmax(S, 0.f), hmin(S, INFINITY);
     std::vector<int> bad(S, 0);
     if (n > 0) {
-        HIPTRY(fill_u32((uint32_t*)d_hmax, 3 * (int64_t)S, 0u, st));
-        HIPTRY(fill_u32((uint32_t*)d_hmin, S, 0x7F800000u, st));   // +inf
+        // (the largest h and the faults from 0, the smallest from +inf)
+        HIPTRY(fill2_u32((uint32_t*)d_hmin, S, 0x7F800000u, (uint32_t*)d_hmax, S, 0u, st));
+        HIPTRY(fill_u32((uint32_t*)d_bad, S, 0u, st));
         int64_t maxc = 0;
         for (int s = 0; s < S; ++s) maxc = std::max<int64_t>(maxc, sets[s].count);
         // a few hundred blocks per set at most: their atomics on one word serialise
@@ -1639,20 +1628,19 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
     hipLaunchKernelGGL(k_top_cells, dim3(nblk(ntop, 256)), dim3(256), 0, st, d_sets, S, (int)ntop, bmax, t->key,
                        t->cells);
     HIPTRY(hipGetLastError());
-    hipLaunchKernelGGL(k_cell_stats, dim3(nblk(ntop, 4)), dim3(256), 0, st, d_sets, bmax, 0, (int64_t)0,
-                       ntop, t->key, t->hdec, prm->n_split, prm->split_frac, t->cells);
-    HIPTRY(hipGetLastError());
-
     // top-level tasks and the split flags of level 0: one read-back for both
     ERRTRY(t->scratch(ntop + 1));
     ERRTRY(t->alloc(t->b_split, sizeof(uint32_t) * (ntop + 1), (void**)&t->split_idx));
+    hipLaunchKernelGGL(k_cell_stats, dim3(nblk(ntop, 4)), dim3(256), 0, st, d_sets, bmax, 0, (int64_t)0,
+                       ntop, t->key, t->hdec, prm->n_split, prm->split_frac, t->cells, t->split_idx);
+    HIPTRY(hipGetLastError());
 #define total (t->d_total)
     hipLaunchKernelGGL(k_top_task_count, dim3(nblk(ntop, 256)), dim3(256), 0, st, d_sets, (int)ntop, t->cells,
                        t->sc_a);
-    HIPTRY(exclusive_scan(t->sc_a, t->sc_b, ntop, t->sc_tmp, total, st));
-    hipLaunchKernelGGL(k_split_flags, dim3(nblk(ntop, 256)), dim3(256), 0, st, t->cells, (int64_t)0, ntop,
-                       t->split_idx);
-    HIPTRY(exclusive_scan(t->split_idx, t->split_idx, ntop, t->sc_tmp, total + 2, st));
+    {
+        const ScanJob jobs[] = {{t->sc_a, t->sc_b, ntop, total}, {t->split_idx, t->split_idx, ntop, total + 2}};
+        HIPTRY(exclusive_scans(jobs, 2, t->sc_tmp, st));
+    }
     const void* rb;
     ERRTRY(read_back(ctx, total, 3 * sizeof(uint32_t), &rb));
     const uint32_t nt0 = ((const uint32_t*)rb)[0];
@@ -1693,16 +1681,13 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
             hipLaunchKernelGGL(k_make_children, dim3(nblk(c1 - c0, 256)), dim3(256), 0, st, c0, c1, c1,
                                t->split_idx, t->cells);
             HIPTRY(hipGetLastError());
-            hipLaunchKernelGGL(k_cell_stats, dim3(nblk(nnext, 4)), dim3(256), 0, st, d_sets, bmax,
-                               level + 1, c1, c1 + nnext, t->key, t->hdec, prm->n_split, prm->split_frac,
-                               t->cells);
-            HIPTRY(hipGetLastError());
             // the children's split flags (the buffer is free once the
             // children exist: a reallocation waits for the device)
             ERRTRY(t->alloc(t->b_split, sizeof(uint32_t) * (nnext + 1), (void**)&t->split_idx));
-            hipLaunchKernelGGL(k_split_flags, dim3(nblk(nnext, 256)), dim3(256), 0, st, t->cells, c1, c1 + nnext,
-                               t->split_idx);
-            HIPTRY(exclusive_scan(t->split_idx, t->split_idx, nnext, t->sc_tmp, total + 2, st));
+            hipLaunchKernelGGL(k_cell_stats, dim3(nblk(nnext, 4)), dim3(256), 0, st, d_sets, bmax,
+                               level + 1, c1, c1 + nnext, t->key, t->hdec, prm->n_split, prm->split_frac,
+                               t->cells, t->split_idx);
+            HIPTRY(hipGetLastError());
         }
         t->lvl_start.push_back(c1 + nnext);
         if (ncur == 0 && nsplit == 0) break;
@@ -1727,8 +1712,12 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
             hipLaunchKernelGGL(k_task_decide, dim3(nblk(ncur, 256)), dim3(256), 0, st, d_sets, t->taskA, ncur,
                                t->cells, t->sc_a, t->sc_c);
             HIPTRY(hipGetLastError());
-            HIPTRY(exclusive_scan(t->sc_a, t->sc_b, ncur, t->sc_tmp, total, st));
-            HIPTRY(exclusive_scan(t->sc_c, t->sc_d, ncur, t->sc_tmp, total + 1, st));
+        }
+        {
+            const ScanJob jobs[] = {{t->sc_a, t->sc_b, ncur, total},
+                                    {t->sc_c, t->sc_d, ncur, total + 1},
+                                    {t->split_idx, t->split_idx, nnext, total + 2}};
+            HIPTRY(exclusive_scans(jobs, 3, t->sc_tmp, st));
         }
         ERRTRY(read_back(ctx, total, 3 * sizeof(uint32_t), &rb));
         const uint32_t nf = ncur > 0 ? ((const uint32_t*)rb)[0] : 0u;
@@ -1757,10 +1746,9 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
     // (the chunk and leaf counts are read back once, at the end)
     const int64_t nc = t->ncells;
     ERRTRY(t->scratch(std::max<int64_t>(nc, t->n) + 1));
-    HIPTRY(fill_u32((uint32_t*)t->d_maxleaf, 2, 0, st));
-    hipLaunchKernelGGL(k_chunk_count, dim3(nblk(nc, 256)), dim3(256), 0, st, t->cells, nc, t->d_maxleaf);
-    HIPTRY(fill_u32(t->sc_c, t->n, 0u, st));
-    hipLaunchKernelGGL(k_chunk_mark, dim3(nblk(nc, 256)), dim3(256), 0, st, t->cells, nc, t->sc_c);
+    // (total[16..20]: leaves, largest leaf; pieces, heavy chunks, sets that are not uneven)
+    HIPTRY(fill2_u32(total + 16, 5, 0u, t->sc_c, t->n, 0u, st));
+    hipLaunchKernelGGL(k_chunk_count, dim3(nblk(nc, 256)), dim3(256), 0, st, t->cells, nc, t->d_maxleaf, t->sc_c);
     HIPTRY(exclusive_scan(t->sc_c, t->sc_d, t->n, t->sc_tmp, total, st));
     // a leaf of k particles gives ceil(k / CHUNK) <= k / CHUNK + 1 chunks
     const int64_t chunk_cap = nc + t->n / CHUNK + 1;
@@ -1829,7 +1817,6 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
     t->order = nullptr;
     if (cost_now && t->try_alloc(t->b_order, 2 * sizeof(uint32_t) * chunk_cap, (void**)&t->pcost))
         t->order = (uint32_t*)(t->pcost + chunk_cap);
-    HIPTRY(fill_u32(total + 18, 3, 0u, st));
     auto chunk_cost = [&]() -> Err {
         hipLaunchKernelGGL(k_chunk_cost, dim3(nblk(chunk_cap, 4)), dim3(256), 0, st, t->chunks, total, chunk_cap,
                            t->cells, d_sets, t->csr_off, t->csr, pieces ? (float)piece_rec : 0.f, t->pcost, t->pcount,
@@ -1988,9 +1975,9 @@ Err sort_pairs(sph_ctx* ctx, sph_tree* t) {
     uint32_t* need = t->sc_a;
     uint32_t* mid_idx = t->sc_c;
     uint32_t* big_idx = t->sc_d;
-    HIPTRY(fill_u32(need, nca, 0, st));
-    unsigned long long* total64 = (unsigned long long*)(t->d_counts + 8);   // 8-byte aligned
-    HIPTRY(fill_u32(t->d_counts + 8, 2, 0u, st));
+    // (in the scratch words, whose reading back reaches it: 8-byte aligned, as 4 * sc_cap + 4 words are)
+    unsigned long long* total64 = (unsigned long long*)(total + 4);
+    HIPTRY(fill2_u32(need, nca, 0u, total + 4, 2, 0u, st));
     const int64_t ne = t->ncsr;
     if (ne > 0) {
         hipLaunchKernelGGL(k_seg_need, dim3(nblk(ne, 256)), dim3(256), 0, st, t->csr, ne, t->ncsr_dev, t->cells,
@@ -2002,18 +1989,17 @@ Err sort_pairs(sph_ctx* ctx, sph_tree* t) {
                            flat ? nullptr : mid_idx, flat ? nullptr : big_idx, total64);
         HIPTRY(hipGetLastError());
     }
-    HIPTRY(exclusive_scan(t->segoff, t->segoff, nca, t->sc_tmp, total, st));
     uint32_t nmid = 0, nbig = 0;
     int64_t nent = 0;
     if (flat) {
-        hipLaunchKernelGGL(k_copy_u32, dim3(1), dim3(64), 0, st, total, t->d_counts, 1);
-        HIPTRY(hipGetLastError());
+        HIPTRY(exclusive_scan(t->segoff, t->segoff, nca, t->sc_tmp, t->d_counts, st));
         nent = NAXES * t->n;   // bound
         t->nsegent = -1;       // exact count on the device
     } else {
-        HIPTRY(exclusive_scan(mid_idx, mid_idx, nca, t->sc_tmp, total + 1, st));
-        HIPTRY(exclusive_scan(big_idx, big_idx, nca, t->sc_tmp, total + 2, st));
-        HIPTRY(hipMemcpyAsync(total + 4, total64, sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
+        const ScanJob jobs[] = {{t->segoff, t->segoff, nca, total},
+                                {mid_idx, mid_idx, nca, total + 1},
+                                {big_idx, big_idx, nca, total + 2}};
+        HIPTRY(exclusive_scans(jobs, 3, t->sc_tmp, st));
         const void* rb;
         ERRTRY(read_back(ctx, total, 6 * sizeof(uint32_t), &rb));
         nmid = ((const uint32_t*)rb)[1];

@@ -36,6 +36,7 @@ struct sph_ctx {
     static constexpr int CTR_CFL = 768;
     static constexpr int CTR_WORK = 1024;
     static constexpr int CTR_PARK = 1600;
+    static constexpr int CTR_DONE = 1664;   // blocks of a Newton step that are done
     static constexpr int CTR_WORDS = 2048;
     // pinned host memory that device counts are read back into: one
     // asynchronous copy per read, then one stream synchronisation
@@ -464,7 +465,7 @@ struct sph_tree {
         n = std::max<int64_t>(n, 1);
         if (n <= sc_cap && sc_a) return sph::Err{};
         int64_t cap = std::max<int64_t>(n, sc_cap * 3 / 2);
-        size_t words = 4 * (size_t)cap + sph::scan_tmp_words(cap) + 64;
+        size_t words = 4 * (size_t)cap + sph::SCAN_JOBS * sph::scan_tmp_words(cap) + 64;
         void* p;
         sph::Err e = alloc(b_sc, words * sizeof(uint32_t), &p);
         if (e.st) return e;

@@ -1826,22 +1826,25 @@ __global__ __launch_bounds__(256) void k_force_pieces(ForceArgs a) {
 // Newton step on h (per particle), ghost, per-cell current h max, scatters,
 // reductions, counters.
 // ---------------------------------------------------------------------------
-__global__ void k_zero_i32(int32_t* p, int n) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+// Counters to clear: by a kernel of their own, or along with the work of one
+// that runs before they are needed (a launch costs as much as either).
+struct Zero {
+    int32_t* p[5];
+    int n[5];
+};
+__device__ __forceinline__ void zero_words(const Zero& z, int64_t i, int64_t stride) {
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+        for (int64_t q = i; q < z.n[k]; q += stride) z.p[k][q] = 0;
 }
-
-// The work counters of an interaction pass, and the slots taken (after a
-// Newton step k_newton has cleared them).
-__global__ void k_zero_ctr(int32_t* p, int n, int32_t* taken) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-    if (i == n) *taken = 0;
+__global__ void k_zero(Zero z) {
+    zero_words(z, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x);
 }
 
 __global__ void k_solve_init(int64_t n, const uint8_t* __restrict__ owned, uint8_t* active, float* lo, float* hi,
-                             float* dstep) {
+                             float* dstep, Zero z) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    zero_words(z, p, (int64_t)gridDim.x * blockDim.x);
     if (p >= n) return;
     active[p] = (!owned || owned[p]) ? 1 : 0;   // a halo particle keeps the h it came with
     lo[p] = 0.f;
@@ -1926,15 +1929,13 @@ __device__ __forceinline__ bool newton_step(int64_t p, uint8_t* __restrict__ act
 
 // The step of every active particle (one thread each); the rare rebuild
 // flags.  The particles still active are counted afterwards (k_count_active).
-// Also clears the work counters (ctr words of ctr) for the next density pass.
-__global__ void k_newton(int64_t n, int32_t* __restrict__ ctr, int nctr, int32_t* __restrict__ taken,
-                         const SetInfo* __restrict__ sets, int nsets, uint8_t* __restrict__ active,
+// Also clears the counters z for the next density pass.
+__global__ void k_newton(int64_t n, Zero z, const SetInfo* __restrict__ sets, int nsets, uint8_t* __restrict__ active,
                          const float* __restrict__ nw, const float* __restrict__ dnw, float* __restrict__ ph,
                          const float* __restrict__ bound, float* __restrict__ lo, float* __restrict__ hi,
                          float* __restrict__ dstep, double target, double tol, int32_t* __restrict__ status) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int64_t i = p; i < nctr; i += (int64_t)gridDim.x * blockDim.x) ctr[i] = 0;
-    if (p == 0) *taken = 0;
+    zero_words(z, p, (int64_t)gridDim.x * blockDim.x);
     if (p >= n || active[p] != 1) return;
     const int s = set_of(sets, nsets, p);
     bool rebuild = false;
@@ -2017,6 +2018,65 @@ __global__ __launch_bounds__(COUNT_BS) void k_count_final(const int4* __restrict
     }
 }
 
+// The two for at most NEWTON_BLOCKS reduction chunks (a chunk is of one set): a
+// block per chunk adds its particles still active to its set's count, and the
+// last block to end writes the counts to status and clears them.  A pass over
+// 10^4 particles takes 20 to 100 us, the launches for step and counts 14 us, one
+// of these 6; with more blocks their atomics on one word take longer than the
+// launches (3906 blocks: 130 us).
+constexpr int NEWTON_BLOCKS = 64, NEWTON_BS = 512;
+__global__ __launch_bounds__(NEWTON_BS) void k_newton_count(const int4* __restrict__ red, Zero z,
+                                                            const SetInfo* __restrict__ sets, int nsets,
+                                                            uint8_t* __restrict__ active,
+                                                            const float* __restrict__ nw,
+                                                            const float* __restrict__ dnw, float* __restrict__ ph,
+                                                            const float* __restrict__ bound, float* __restrict__ lo,
+                                                            float* __restrict__ hi, float* __restrict__ dstep,
+                                                            double target, double tol, int32_t* __restrict__ status,
+                                                            int* cnt, int* done) {
+    const int4 R = red[blockIdx.x];
+    if (blockIdx.x == 0) zero_words(z, threadIdx.x, NEWTON_BS);
+    const double hcap = 0.5 * sets[R.x].box;
+    int c = 0;
+    for (int p = R.y + (int)threadIdx.x; p < R.y + R.z; p += NEWTON_BS) {
+        bool rebuild = false;
+        c += newton_step(p, active, nw, dnw, ph, bound, lo, hi, dstep, target, tol, hcap, rebuild) ? 1 : 0;
+        if (rebuild) {
+            atomicExch(&status[0], 1);
+            atomicExch(&status[2 + 2 * R.x], 1);
+        }
+    }
+    __shared__ int s_c[NEWTON_BS / 64], s_last;
+    for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+    if ((threadIdx.x & 63) == 0) s_c[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        c = 0;
+        for (int k = 0; k < NEWTON_BS / 64; ++k) c += s_c[k];
+        // (the count is added before the block is done: its old value is waited for)
+        int old = atomicAdd(&cnt[R.x], c);
+        asm volatile("" : "+v"(old) : : "memory");
+        s_last = atomicAdd(done, old < 0 ? 0 : 1) == (int)gridDim.x - 1 ? 1 : 0;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    int tot = 0;
+    for (int s = threadIdx.x; s < nsets; s += NEWTON_BS) {
+        const int v = atomicExch(&cnt[s], 0);
+        status[3 + 2 * s] = v;
+        tot += v;
+    }
+    for (int d = 32; d >= 1; d >>= 1) tot += __shfl_xor(tot, d, 64);
+    if ((threadIdx.x & 63) == 0) s_c[threadIdx.x >> 6] = tot;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        tot = 0;
+        for (int k = 0; k < NEWTON_BS / 64; ++k) tot += s_c[k];
+        status[1] = tot;
+        atomicExch(done, 0);
+    }
+}
+
 // Outputs in caller order are written in that order (coalesced), each read
 // from its cell-order slot through the inverse permutation.
 __global__ void k_save_state(int64_t n, const uint32_t* __restrict__ iperm, const uint8_t* active, const float* lo,
@@ -2059,8 +2119,9 @@ __global__ void k_load_state(int64_t n, const uint32_t* __restrict__ perm, uint8
 
 __global__ void k_ghost(int64_t n, const float* __restrict__ ph, const float* __restrict__ rho,
                         const float* __restrict__ drho, const float* __restrict__ u, float gamma,
-                        float4* __restrict__ frec, float4* __restrict__ pv) {
+                        float4* __restrict__ frec, float4* __restrict__ pv, Zero z) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    zero_words(z, p, (int64_t)gridDim.x * blockDim.x);
     if (p >= n) return;
     const float r = rho[p], h = ph[p];
     const float P = (gamma - 1.f) * r * u[p];
@@ -2379,7 +2440,8 @@ static void launch_teams(const sph_ctx* ctx, const sph_tree* t, const A& a, int6
 
 // listed: a Newton pass after the first, over the chunks that still hold
 // active particles (k_chunk_list; its counts sit in the context's counter
-// block after the force counters; the Newton step cleared them all)
+// block after the force counters; the Newton step cleared them all; before a
+// first pass the caller does)
 static bool ext_kernels(const sph_tree* t) { return t->ext(); }
 
 static void launch_density(sph_ctx* ctx, sph_tree* t, bool solve, bool listed, int* counter) {
@@ -2391,8 +2453,6 @@ static void launch_density(sph_ctx* ctx, sph_tree* t, bool solve, bool listed, i
         const int bpg = (int)((t->nchunks / NGRP + LIST_BS) / LIST_BS);
         hipLaunchKernelGGL(k_chunk_list, dim3(NGRP * bpg), dim3(LIST_BS), 0, st, t->chunks, (int)t->nchunks, bpg,
                            t->active, t->order, t->alist, lcount);
-    } else {
-        hipLaunchKernelGGL(k_zero_ctr, dim3(2), dim3(256), 0, st, counter, NGRP * CSTRIDE, taken);
     }
     DensArgs a = dens_args(t, counter, lcount);
     a.taken = taken;
@@ -2446,15 +2506,16 @@ __global__ __launch_bounds__(256) void k_block_h(const float4* __restrict__ frec
 static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     hipStream_t st = ctx->stream;
     const int64_t n = t->n;
+    int* taken = ctx->d_counter + sph_ctx::CTR_PARK + CSTRIDE;
+    t->work_ctr = ctx->d_counter + sph_ctx::CTR_WORK;
     hipLaunchKernelGGL(k_ghost, dim3(nblk(n, 256)), dim3(256), 0, st, n, t->ph, t->rho, t->drho, t->pu,
-                       t->prm.gamma, t->frec, t->pv);
+                       t->prm.gamma, t->frec, t->pv,
+                       Zero{{t->work_ctr + 256, counter, taken}, {256, NGRP * CSTRIDE, 1}});
     hipLaunchKernelGGL(k_cell_hcur, dim3(nblk(t->ncells, 4)), dim3(256), 0, st, t->cells, t->ncells, t->ph, t->segoff,
                        t->segidx);
     if (t->blkbox && t->ext())
         hipLaunchKernelGGL(k_block_h, dim3((unsigned)std::min<int64_t>(nblk(t->nblk, 4), 65535)), dim3(256), 0, st,
                            t->frec, n, t->nblk, t->blkbox);
-    int* taken = ctx->d_counter + sph_ctx::CTR_PARK + CSTRIDE;
-    hipLaunchKernelGGL(k_zero_ctr, dim3(2), dim3(256), 0, st, counter, NGRP * CSTRIDE, taken);
     ev_mark(ctx, "ghost");
     ForceArgs a;
     a.taken = taken;
@@ -2521,13 +2582,22 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     }
 }
 
-// A Newton step of every active particle (DENS_CTR: the density, force and
-// chunk-list counters).
+// The counters of the density passes, and those of the chunk lists (after
+// the force pass's).
 constexpr int DENS_CTR = 3 * NGRP * CSTRIDE;
+static Zero density_ctr(sph_ctx* ctx, sph_tree* t) {
+    t->work_ctr = ctx->d_counter + sph_ctx::CTR_WORK;
+    return Zero{{t->work_ctr, ctx->d_counter, ctx->d_counter + sph_ctx::CTR_PARK}, {256, NGRP * CSTRIDE, 1}};
+}
+
+// A Newton step of every active particle.
+static Zero newton_ctr(sph_ctx* ctx) {
+    return Zero{{ctx->d_counter, ctx->d_counter + sph_ctx::CTR_PARK}, {DENS_CTR, 1}};
+}
 static void launch_newton(sph_ctx* ctx, sph_tree* t) {
-    hipLaunchKernelGGL(k_newton, dim3(nblk(t->n, 256)), dim3(256), 0, ctx->stream, t->n, ctx->d_counter, DENS_CTR,
-                       ctx->d_counter + sph_ctx::CTR_PARK, t->d_sets, t->nsets, t->active, t->nw, t->dnw, t->ph,
-                       t->bound, t->lo, t->hi, t->dstep, (double)t->prm.n_target, (double)t->prm.h_tol, t->status);
+    hipLaunchKernelGGL(k_newton, dim3(nblk(t->n, 256)), dim3(256), 0, ctx->stream, t->n, newton_ctr(ctx), t->d_sets,
+                       t->nsets, t->active, t->nw, t->dnw, t->ph, t->bound, t->lo, t->hi, t->dstep,
+                       (double)t->prm.n_target, (double)t->prm.h_tol, t->status);
 }
 
 // status[1] and status[3+2s] = particles still active after the last Newton
@@ -2537,6 +2607,20 @@ static void launch_count(sph_ctx* ctx, sph_tree* t) {
                        t->part_cnt);
     hipLaunchKernelGGL(k_count_final, dim3(1), dim3(COUNT_BS), 0, ctx->stream, t->d_red, (int)t->nred, t->part_cnt,
                        t->nsets, t->status);
+}
+
+// The step and the counts after it (the counts per set start at zero, see
+// solve_ctr; a set has at least one reduction chunk).
+static void launch_newton_count(sph_ctx* ctx, sph_tree* t) {
+    if (t->nred > NEWTON_BLOCKS) {
+        launch_newton(ctx, t);
+        launch_count(ctx, t);
+        return;
+    }
+    hipLaunchKernelGGL(k_newton_count, dim3((unsigned)t->nred), dim3(NEWTON_BS), 0, ctx->stream, t->d_red,
+                       newton_ctr(ctx), t->d_sets, t->nsets, t->active, t->nw, t->dnw, t->ph, t->bound, t->lo, t->hi,
+                       t->dstep, (double)t->prm.n_target, (double)t->prm.h_tol, t->status, t->part_cnt,
+                       ctx->d_counter + sph_ctx::CTR_DONE);
 }
 
 static void launch_reduce(sph_ctx* ctx, sph_tree* t, double* sums_out) {
@@ -2560,20 +2644,13 @@ static void launch_scatter_force(sph_ctx* ctx, sph_tree* t, const sph_force_out*
                        t->fay, t->faz, t->fdu, t->fvs, t->fS, t->fn, t->hash ? t->hashf : nullptr, t->owned, *o);
 }
 
-// The pair-evaluation counters of a stage start at zero (density: words
-// [0, 256), force: [256, 512) of the work block of the context's counters).
-static void zero_work(sph_ctx* ctx, sph_tree* t, int first, int words) {
-    t->work_ctr = ctx->d_counter + sph_ctx::CTR_WORK;
-    hipLaunchKernelGGL(k_zero_i32, dim3(2), dim3(256), 0, ctx->stream, t->work_ctr + first, words);
-}
-
 Err run_density(sph_ctx* ctx, sph_tree* t, const sph_density_out* out) {
     if (!t->built || !t->sorted) return Err{SPH_E_STATE, "density before build_cells/sort_pairs"};
     if (out && out->hash && !t->hash) return Err{SPH_E_ARG, "pair hash requested without SPH_FLAG_PAIR_HASH"};
     ERRTRY(ensure_state(ctx, t));
     if (t->n == 0) return Err{};
     ev_mark(ctx, "start");
-    zero_work(ctx, t, 0, 256);
+    hipLaunchKernelGGL(k_zero, dim3(1), dim3(256), 0, ctx->stream, density_ctr(ctx, t));
     launch_density(ctx, t, false, false, ctx->d_counter);
     ev_mark(ctx, "density");
     launch_scatter_density(ctx, t, out);
@@ -2581,6 +2658,19 @@ Err run_density(sph_ctx* ctx, sph_tree* t, const sph_density_out* out) {
     ev_mark(ctx, "scatter");
     t->have_density = true;
     return Err{};
+}
+
+// What a solve starts from: the density pass's counters, no blocks done, no
+// particles counted, status.
+static Zero solve_ctr(sph_ctx* ctx, sph_tree* t) {
+    Zero z = density_ctr(ctx, t);
+    static_assert(sph_ctx::CTR_DONE == sph_ctx::CTR_PARK + 2 * CSTRIDE, "cleared with the slots taken");
+    z.n[2] = 2 * CSTRIDE + 1;
+    z.p[3] = t->status;
+    z.n[3] = 2 + 2 * t->nsets;
+    z.p[4] = t->part_cnt;
+    z.n[4] = t->nsets;
+    return z;
 }
 
 Err run_solve(sph_ctx* ctx, sph_tree* t, const sph_density_out* out, int32_t* n_unconv, int32_t* iters) {
@@ -2595,19 +2685,18 @@ Err run_solve(sph_ctx* ctx, sph_tree* t, const sph_density_out* out, int32_t* n_
     if (iters) *iters = 0;
     if (n == 0) return Err{};
     ev_mark(ctx, "start");
+    const Zero zero = solve_ctr(ctx, t);
     const bool resume = (t->prm.flags & SPH_FLAG_RESUME) && t->saved && t->saved_n == n;
     if (resume) {
         hipLaunchKernelGGL(k_load_state, dim3(nblk(n, 256)), dim3(256), 0, st, n, t->perm, t->active, t->lo, t->hi,
                            t->dstep, t->rho, t->drho, t->nw, t->dnw, t->nngb, t->hash ? t->hashd : nullptr,
                            t->saved_state());
+        hipLaunchKernelGGL(k_zero, dim3(1), dim3(256), 0, st, zero);
     } else {
         hipLaunchKernelGGL(k_solve_init, dim3(nblk(n, 256)), dim3(256), 0, st, n, t->owned, t->active, t->lo,
-                           t->hi, t->dstep);
+                           t->hi, t->dstep, zero);
     }
     t->saved = false;
-    const int nst = 2 + 2 * t->nsets;
-    hipLaunchKernelGGL(k_zero_i32, dim3(nblk(nst, 256)), dim3(256), 0, st, t->status, nst);
-    zero_work(ctx, t, 0, 256);
     // Each pass is enqueued before the host reads the status of the one
     // before, so the device runs pass k + 1 while the host waits for pass
     // k's counts (no idle gap per pass).  A pass enqueued after the last
@@ -2620,8 +2709,7 @@ Err run_solve(sph_ctx* ctx, sph_tree* t, const sph_density_out* out, int32_t* n_
         ev_mark(ctx, "newton");
         launch_density(ctx, t, true, k > 0, ctx->d_counter);
         ev_mark(ctx, "density_pass");
-        launch_newton(ctx, t);
-        launch_count(ctx, t);
+        launch_newton_count(ctx, t);
         hipError_t e = hipGetLastError();
         if (e == hipSuccess) e = hipMemcpyAsync(slots + 2 * (k & 1), t->status, 2 * sizeof(int32_t),
                                                 hipMemcpyDeviceToHost, st);
@@ -2687,7 +2775,6 @@ Err run_force(sph_ctx* ctx, sph_tree* t, const sph_force_out* out) {
     ERRTRY(ensure_state(ctx, t));
     if (t->n == 0) return Err{};
     ev_mark(ctx, "start");
-    zero_work(ctx, t, 256, 256);
     launch_force(ctx, t, ctx->d_counter + NGRP * CSTRIDE);
     ev_mark(ctx, "force");
     launch_reduce(ctx, t, out ? out->sums : nullptr);
@@ -2816,10 +2903,7 @@ Err run_graph(sph_ctx* ctx, sph_tree* t, int k_iter, const sph_density_out* dout
         hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
             hipLaunchKernelGGL(k_solve_init, dim3(nblk(n, 256)), dim3(256), 0, st, n, t->owned, t->active, t->lo,
-                               t->hi, t->dstep);
-            zero_work(ctx, t, 0, 512);
-            const int nst = 2 + 2 * t->nsets;
-            hipLaunchKernelGGL(k_zero_i32, dim3(nblk(nst, 256)), dim3(256), 0, st, t->status, nst);
+                               t->hi, t->dstep, solve_ctr(ctx, t));
             for (int it = 0; it < k_iter; ++it) {
                 launch_density(ctx, t, true, it > 0, ctx->d_counter);
                 launch_newton(ctx, t);

@@ -9,6 +9,16 @@ size_t scan_tmp_words(int64_t n);
 // out[i] = sum_{k<i} in[k] (in may equal out); *total (device, nullable) = sum.
 hipError_t exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* tmp, uint32_t* total,
                           hipStream_t st);
+// Up to three such scans in the launches of one (tmp: three times the scratch
+// of the longest).
+struct ScanJob {
+    const uint32_t* in;
+    uint32_t* out;
+    int64_t n;
+    uint32_t* total;
+};
+constexpr int SCAN_JOBS = 3;
+hipError_t exclusive_scans(const ScanJob* jobs, int njobs, uint32_t* tmp, hipStream_t st);
 
 // Words of uint32 scratch a radix sort of n elements needs.
 size_t radix_tmp_words(int64_t n);
@@ -20,5 +30,7 @@ hipError_t radix_sort(uint64_t* key, uint32_t* val, uint64_t* key_alt, uint32_t*
                       int nbits, uint32_t* tmp, hipStream_t st, bool* result_in_alt, int lo_bit = 0);
 
 hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
+// two arrays in one launch
+hipError_t fill2_u32(uint32_t* p, int64_t n, uint32_t v, uint32_t* p2, int64_t n2, uint32_t v2, hipStream_t st);
 
 }  // namespace sph
