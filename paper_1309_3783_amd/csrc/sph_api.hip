@@ -125,12 +125,13 @@ sph_status sph_ctx_create(sph_ctx** out, int device, void* stream) {
         delete c;
         return SPH_E_WORKSPACE;
     }
-    if (hipHostMalloc(&c->h_pin, sph_ctx::PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&c->h_pin, sph_ctx::PIN_BYTES, hipHostMallocCoherent) != hipSuccess) {
         c->h_pin = nullptr;
         (void)hipFree(c->d_counter);
         delete c;
         return SPH_E_WORKSPACE;
     }
+    std::memset(c->h_pin, 0, sph_ctx::PIN_BYTES);
     *out = c;
     return SPH_OK;
 }
@@ -138,8 +139,6 @@ sph_status sph_ctx_create(sph_ctx** out, int device, void* stream) {
 void sph_ctx_destroy(sph_ctx* ctx) {
     if (!ctx) return;
     for (auto& e : ctx->ev_pool) (void)hipEventDestroy(e);
-    for (auto& e : ctx->solve_ev)
-        if (e) (void)hipEventDestroy(e);
     if (ctx->d_counter) (void)hipFree(ctx->d_counter);
     if (ctx->h_pin) (void)hipHostFree(ctx->h_pin);
     delete ctx;

@@ -16,7 +16,9 @@
 // the level loop reads one count back per level to size the next one.
 #include <algorithm>
 #include <cmath>
+#include <chrono>
 #include <cstring>
+#include <thread>
 
 #include "sph_impl.h"
 
@@ -1421,14 +1423,51 @@ static inline unsigned nblk(int64_t n, int bs) { return (unsigned)((n + bs - 1) 
         if (e_.st != SPH_OK) return e_;    \
     } while (0)
 
-// Device words read back through the context's pinned buffer: one
-// asynchronous copy, one stream synchronisation.
+Err wait_pinned(sph_ctx* ctx, const uint32_t* word, uint32_t seq, bool behind) {
+    auto written = [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) == seq; };
+    const auto t0 = std::chrono::steady_clock::now();
+    while (!written()) {
+        if (std::chrono::steady_clock::now() - t0 < std::chrono::microseconds(SPIN_US)) continue;
+        if (!behind) {
+            HIPTRY(hipStreamSynchronize(ctx->stream));
+        } else {
+            const hipError_t e = hipStreamQuery(ctx->stream);
+            if (e == hipErrorNotReady) {
+                std::this_thread::sleep_for(std::chrono::microseconds(20));
+                continue;
+            }
+            HIPTRY(e);
+        }
+        if (!written()) return Err{SPH_E_STATE, "internal: counts not written"};
+    }
+    return Err{};
+}
+
+// Device words read back through the context's pinned buffer, by a kernel (a
+// copy goes by one as well).
+__global__ __launch_bounds__(256) void k_publish(const uint32_t* __restrict__ src, int n, uint32_t* dst,
+                                                 uint32_t* done, uint32_t seq) {
+    for (int i = threadIdx.x; i < n; i += 256)
+        __hip_atomic_store(dst + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(done, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 static Err read_back(sph_ctx* ctx, const void* d, size_t bytes, const void** h) {
     if (bytes > sph_ctx::PIN_BYTES) return Err{SPH_E_STATE, "internal: read-back larger than the pinned buffer"};
-    HIPTRY(hipMemcpyAsync(ctx->h_pin, d, bytes, hipMemcpyDeviceToHost, ctx->stream));
-    HIPTRY(hipStreamSynchronize(ctx->stream));
+    uint32_t* done = (uint32_t*)((char*)ctx->h_pin + sph_ctx::PIN_DONE);
     *h = ctx->h_pin;
-    return Err{};
+    if (bytes > sph_ctx::PIN_SOLVE || bytes % sizeof(uint32_t)) {
+        HIPTRY(hipMemcpyAsync(ctx->h_pin, d, bytes, hipMemcpyDeviceToHost, ctx->stream));
+        HIPTRY(hipStreamSynchronize(ctx->stream));
+        return Err{};
+    }
+    const uint32_t seq = ctx->next_seq();
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, ctx->stream, (const uint32_t*)d,
+                       (int)(bytes / sizeof(uint32_t)), (uint32_t*)ctx->h_pin, done, seq);
+    HIPTRY(hipGetLastError());
+    return wait_pinned(ctx, done, seq, false);
 }
 
 // Block summaries of the particle array, for a tree whose interaction

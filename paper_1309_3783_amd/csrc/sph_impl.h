@@ -38,18 +38,26 @@ struct sph_ctx {
     static constexpr int CTR_PARK = 1600;
     static constexpr int CTR_DONE = 1664;   // blocks of a Newton step that are done
     static constexpr int CTR_WORDS = 2048;
-    // pinned host memory that device counts are read back into: one
-    // asynchronous copy per read, then one stream synchronisation
+    // pinned host memory that kernels write counts to, each write followed
+    // by its number (pin_seq, never zero) which the host waits for: at PIN_DONE
+    // for those read back, in each of the two slots of the Newton loop's
+    // status words at PIN_SOLVE
     static constexpr size_t PIN_BYTES = 65536;
-    void* h_pin = nullptr;
-    // the Newton loop's status words, two slots at this offset of h_pin,
-    // and the events that mark their copies done
     static constexpr size_t PIN_SOLVE = 32768;
-    hipEvent_t solve_ev[2] = {nullptr, nullptr};
+    static constexpr size_t PIN_DONE = 49152;
+    void* h_pin = nullptr;
+    uint32_t pin_seq = 0;
+    uint32_t next_seq() { return ++pin_seq ? pin_seq : ++pin_seq; }
     hipStream_t cap_stream = nullptr; // private stream used only to capture graphs
 };
 
 namespace sph {
+// Wait for a kernel's number in pinned memory.  The host polls for SPIN_US
+// (most waits; hipStreamSynchronize takes some 10 us longer to return), then
+// sleeps between looks; behind: more work may be enqueued behind the write.
+constexpr int SPIN_US = 1000;
+Err wait_pinned(sph_ctx* ctx, const uint32_t* word, uint32_t seq, bool behind);
+
 // Sub-allocator over one device region that the caller provides (a tree's
 // workspace): first fit over a free list of 256-byte granules, neighbouring
 // free blocks merged.  Blocks are given back and handed out again in stream

@@ -1946,6 +1946,19 @@ __global__ void k_newton(int64_t n, Zero z, const SetInfo* __restrict__ sets, in
     }
 }
 
+// Status words [0] and [1] for the host: to pinned memory, then their number
+// (p null: not wanted).
+struct HostWords {
+    int32_t* p;
+    uint32_t seq;
+    __device__ __forceinline__ void write(int32_t a, int32_t b) const {
+        if (!p) return;
+        __hip_atomic_store(p, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(p + 1, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store((uint32_t*)p + 2, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+};
+
 // Particles still active, per reduction chunk (one block each) ...
 __global__ __launch_bounds__(256) void k_count_active(const int4* __restrict__ red, const uint8_t* __restrict__ active,
                                                       int32_t* __restrict__ part) {
@@ -1976,7 +1989,7 @@ __device__ __forceinline__ int first_red_chunk(const int4* __restrict__ red, int
 constexpr int COUNT_BS = 1024;
 __global__ __launch_bounds__(COUNT_BS) void k_count_final(const int4* __restrict__ red, int nred,
                                                           const int32_t* __restrict__ part, int nsets,
-                                                          int32_t* __restrict__ status) {
+                                                          int32_t* __restrict__ status, HostWords host) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     __shared__ int s_w[COUNT_BS / 64];
     if (nsets <= COUNT_BS / 64) {
@@ -1996,7 +2009,10 @@ __global__ __launch_bounds__(COUNT_BS) void k_count_final(const int4* __restrict
             }
             __syncthreads();
         }
-        if (threadIdx.x == 0) status[1] = tot;
+        if (threadIdx.x == 0) {
+            status[1] = tot;
+            host.write(status[0], tot);
+        }
         return;
     }
     int tot = 0;
@@ -2015,6 +2031,7 @@ __global__ __launch_bounds__(COUNT_BS) void k_count_final(const int4* __restrict
         int t = 0;
         for (int k = 0; k < COUNT_BS / 64; ++k) t += s_w[k];
         status[1] = t;
+        host.write(status[0], t);
     }
 }
 
@@ -2033,7 +2050,7 @@ __global__ __launch_bounds__(NEWTON_BS) void k_newton_count(const int4* __restri
                                                             const float* __restrict__ bound, float* __restrict__ lo,
                                                             float* __restrict__ hi, float* __restrict__ dstep,
                                                             double target, double tol, int32_t* __restrict__ status,
-                                                            int* cnt, int* done) {
+                                                            int* cnt, int* done, HostWords host) {
     const int4 R = red[blockIdx.x];
     if (blockIdx.x == 0) zero_words(z, threadIdx.x, NEWTON_BS);
     const double hcap = 0.5 * sets[R.x].box;
@@ -2042,7 +2059,8 @@ __global__ __launch_bounds__(NEWTON_BS) void k_newton_count(const int4* __restri
         bool rebuild = false;
         c += newton_step(p, active, nw, dnw, ph, bound, lo, hi, dstep, target, tol, hcap, rebuild) ? 1 : 0;
         if (rebuild) {
-            atomicExch(&status[0], 1);
+            int old = atomicExch(&status[0], 1);   // (set before the block is done, as the count below)
+            asm volatile("" : "+v"(old) : : "memory");
             atomicExch(&status[2 + 2 * R.x], 1);
         }
     }
@@ -2074,6 +2092,7 @@ __global__ __launch_bounds__(NEWTON_BS) void k_newton_count(const int4* __restri
         for (int k = 0; k < NEWTON_BS / 64; ++k) tot += s_c[k];
         status[1] = tot;
         atomicExch(done, 0);
+        host.write(__hip_atomic_load(&status[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), tot);
     }
 }
 
@@ -2602,25 +2621,25 @@ static void launch_newton(sph_ctx* ctx, sph_tree* t) {
 
 // status[1] and status[3+2s] = particles still active after the last Newton
 // step (written, not accumulated: nothing to clear first)
-static void launch_count(sph_ctx* ctx, sph_tree* t) {
+static void launch_count(sph_ctx* ctx, sph_tree* t, HostWords host) {
     hipLaunchKernelGGL(k_count_active, dim3((unsigned)t->nred), dim3(256), 0, ctx->stream, t->d_red, t->active,
                        t->part_cnt);
     hipLaunchKernelGGL(k_count_final, dim3(1), dim3(COUNT_BS), 0, ctx->stream, t->d_red, (int)t->nred, t->part_cnt,
-                       t->nsets, t->status);
+                       t->nsets, t->status, host);
 }
 
 // The step and the counts after it (the counts per set start at zero, see
 // solve_ctr; a set has at least one reduction chunk).
-static void launch_newton_count(sph_ctx* ctx, sph_tree* t) {
+static void launch_newton_count(sph_ctx* ctx, sph_tree* t, HostWords host) {
     if (t->nred > NEWTON_BLOCKS) {
         launch_newton(ctx, t);
-        launch_count(ctx, t);
+        launch_count(ctx, t, host);
         return;
     }
     hipLaunchKernelGGL(k_newton_count, dim3((unsigned)t->nred), dim3(NEWTON_BS), 0, ctx->stream, t->d_red,
                        newton_ctr(ctx), t->d_sets, t->nsets, t->active, t->nw, t->dnw, t->ph, t->bound, t->lo, t->hi,
                        t->dstep, (double)t->prm.n_target, (double)t->prm.h_tol, t->status, t->part_cnt,
-                       ctx->d_counter + sph_ctx::CTR_DONE);
+                       ctx->d_counter + sph_ctx::CTR_DONE, host);
 }
 
 static void launch_reduce(sph_ctx* ctx, sph_tree* t, double* sums_out) {
@@ -2701,20 +2720,17 @@ Err run_solve(sph_ctx* ctx, sph_tree* t, const sph_density_out* out, int32_t* n_
     // before, so the device runs pass k + 1 while the host waits for pass
     // k's counts (no idle gap per pass).  A pass enqueued after the last
     // one needed finds no active particle: an empty chunk list, no Newton
-    // step, no change.  The status words of pass k go to pinned slot k mod 2.
-    for (auto& e : ctx->solve_ev)
-        if (!e) HIPTRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    // step, no change.  The kernel that counts writes the status words of
+    // pass k to pinned slot k mod 2.
     int32_t* slots = (int32_t*)((char*)ctx->h_pin + sph_ctx::PIN_SOLVE);
+    uint32_t seq[2] = {0, 0};
     auto enqueue = [&](int k) -> hipError_t {
         ev_mark(ctx, "newton");
         launch_density(ctx, t, true, k > 0, ctx->d_counter);
         ev_mark(ctx, "density_pass");
-        launch_newton_count(ctx, t);
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess) e = hipMemcpyAsync(slots + 2 * (k & 1), t->status, 2 * sizeof(int32_t),
-                                                hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipEventRecord(ctx->solve_ev[k & 1], st);
-        return e;
+        seq[k & 1] = ctx->next_seq();
+        launch_newton_count(ctx, t, HostWords{slots + 4 * (k & 1), seq[k & 1]});
+        return hipGetLastError();
     };
     int32_t hstat[2] = {0, 0};
     int it = 0, enq = 1;
@@ -2725,9 +2741,10 @@ Err run_solve(sph_ctx* ctx, sph_tree* t, const sph_density_out* out, int32_t* n_
             HIPTRY(enqueue(k + 1));
             enq = k + 2;
         }
-        HIPTRY(hipEventSynchronize(ctx->solve_ev[k & 1]));
-        hstat[0] = slots[2 * (k & 1)];
-        hstat[1] = slots[2 * (k & 1) + 1];
+        const int32_t* slot = slots + 4 * (k & 1);
+        ERRTRY(wait_pinned(ctx, (const uint32_t*)slot + 2, seq[k & 1], true));
+        hstat[0] = slot[0];
+        hstat[1] = slot[1];
         it = k + 1;
         if (hstat[1] == 0) break;
     }
@@ -2909,7 +2926,7 @@ Err run_graph(sph_ctx* ctx, sph_tree* t, int k_iter, const sph_density_out* dout
                 launch_newton(ctx, t);
             }
             // only the state after the last step is reported
-            launch_count(ctx, t);
+            launch_count(ctx, t, HostWords{});
             launch_density(ctx, t, true, k_iter > 0, ctx->d_counter);
             launch_force(ctx, t, ctx->d_counter + NGRP * CSTRIDE);
             launch_reduce(ctx, t, fout ? fout->sums : nullptr);
