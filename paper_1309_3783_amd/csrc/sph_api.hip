@@ -162,7 +162,7 @@ sph_status sph_workspace_size(int64_t n, int32_t nsets, const sph_params* p, siz
     // Per particle: 124 B of cell-ordered state (keys and values twice,
     // permutations, position and remainder, velocity, h, u, bounds, pair-hash
     // terms), 48 B of the caller's data packed for the gather, 28 B density,
-    // 13 B solve, 52 B force, 41 B saved Newton state, 16 B of radix and
+    // 13 B solve, 52 B force, 40 B saved Newton state, 16 B of radix and
     // scan scratch: ~323 B.  Sorted lists: 20 B per entry,
     // 13 entries per particle and tree level that holds pair tasks (29 per
     // particle on a clustered set with h over three decades: 580 B), plus

@@ -1057,6 +1057,7 @@ __global__ __launch_bounds__(256) void k_cell_nsmall(const SetInfo* sets, Cell* 
     if (c >= nc) return;
     const int lane = threadIdx.x & 63;
     const Cell C = cells[c];
+    if (C.count == 0) return;   // (zero since the cell was made)
     const float lim = small_h_limit(sets, C);
     int k = 0;
 #pragma unroll 8

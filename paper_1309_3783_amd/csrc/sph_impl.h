@@ -406,7 +406,7 @@ struct sph_tree {
     sph::SolveState saved_state() const { return sv; }
 
     static size_t saved_bytes(int64_t m) {
-        return (size_t)m * (1 + 7 * sizeof(float) + sizeof(int32_t) + sizeof(uint64_t)) + 256;
+        return (2 * sizeof(float4) + sizeof(uint64_t)) * (size_t)m;
     }
 
     sph::Err ensure_saved() {
@@ -419,16 +419,8 @@ struct sph_tree {
     }
 
     void layout_saved(void* p, int64_t m) {
-        sv.hash = (uint64_t*)p;
-        sv.lo = (float*)(sv.hash + m);
-        sv.hi = sv.lo + m;
-        sv.dstep = sv.hi + m;
-        sv.rho = sv.dstep + m;
-        sv.drho = sv.rho + m;
-        sv.nw = sv.drho + m;
-        sv.dnw = sv.nw + m;
-        sv.nngb = (int32_t*)(sv.dnw + m);
-        sv.active = (uint8_t*)(sv.nngb + m);
+        sv.rec = (float4*)p;
+        sv.hash = (uint64_t*)(sv.rec + 2 * m);
     }
 
     // Attach a caller-provided workspace (null: go back to one hipMalloc per

@@ -126,9 +126,7 @@ static_assert(sizeof(Cell) == 64, "Cell layout");
 // Newton state of a solve interrupted by a rebuild, kept in caller order so
 // that the solve on the rebuilt tree continues where it stopped.
 struct SolveState {
-    uint8_t* active;
-    float *lo, *hi, *dstep, *rho, *drho, *nw, *dnw;
-    int32_t* nngb;
+    float4* rec;      // two per particle, see k_save_state
     uint64_t* hash;
 };
 
