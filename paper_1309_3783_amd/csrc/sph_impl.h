@@ -200,6 +200,7 @@ struct sph_tree {
     // or every chunk from its start
     int64_t nslots = 0;
     bool direct = false;
+    bool direct_density = false;
     int64_t nplain = 0;          // sets with particles that are not uneven (see SetInfo), where a tree is ext()
     float* pcost = nullptr;      // per chunk: the records its walk is estimated to read
     uint32_t* order = nullptr;   // each range's chunks, the longest walks first (null: in their own order)

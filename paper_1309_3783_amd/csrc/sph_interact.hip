@@ -2340,6 +2340,11 @@ static Err ensure_state(const sph_ctx* ctx, sph_tree* t) {
     // for the walks they park, where the tree has long walks at all.  More than PARK_SLOTS
     // walks (eight per CU) parked at a time would be no tail.
     t->direct = t->ext() && t->nplain == 0 && t->npieces == 0 && t->nchunks <= 20 * (int64_t)ctx->n_cu;
+    // The density sums of a set of one level are added up tile by tile too, so
+    // blocks walk a few chunks of those (16927 particles, 512 chunks: the h
+    // solve and force 510 us by waves, 436 by blocks; 250047, 4111 chunks, by
+    // blocks 594 against 510).  The force's du and S are not (ForceP::fold).
+    t->direct_density = t->direct || (!t->ext() && t->nchunks <= 8 * (int64_t)ctx->n_cu);
     t->nslots = t->ext() && !t->direct ? std::min<int64_t>(t->nchunks, PARK_SLOTS) : 0;
     if (t->nslots > 0 && !t->try_alloc(t->b_park, (size_t)PARK_BYTES * t->nslots, &p)) t->nslots = 0;
     // reduction chunks: RED_CHUNK particles of one set each
@@ -2453,9 +2458,9 @@ static DensArgs dens_args(sph_tree* t, int* counter, const int* lcount) {
 // against 1.12 with four and 1.15 with sixteen), four where the chunks are
 // more than fit (200000 particles: 3.5 against 4.2 ms with two).
 template <class A, class F>
-static void launch_teams(const sph_ctx* ctx, const sph_tree* t, const A& a, int64_t items, F kern) {
-    const bool wide = items <= 4 * (int64_t)ctx->n_cu || !t->direct;
-    int64_t blocks = t->direct ? items : std::min<int64_t>(items, 2 * (int64_t)ctx->n_cu);
+static void launch_teams(const sph_ctx* ctx, const sph_tree* t, const A& a, int64_t items, bool chunks, F kern) {
+    const bool wide = items <= 4 * (int64_t)ctx->n_cu || !chunks;
+    int64_t blocks = chunks ? items : std::min<int64_t>(items, 2 * (int64_t)ctx->n_cu);
     if (t->prm.blocks_per_cu > 0) blocks = std::min<int64_t>(blocks, (int64_t)ctx->n_cu * t->prm.blocks_per_cu);
     const dim3 grid((unsigned)std::max<int64_t>(1, blocks));
     if (wide) hipLaunchKernelGGL(kern(std::integral_constant<int, 8>{}), grid, dim3(512), 0, ctx->stream, a);
@@ -2480,8 +2485,8 @@ static void launch_density(sph_ctx* ctx, sph_tree* t, bool solve, bool listed, i
     }
     DensArgs a = dens_args(t, counter, lcount);
     a.taken = taken;
-    if (t->direct) {
-        launch_teams(ctx, t, a, t->nchunks, [&](auto W) {
+    if (t->direct_density) {
+        launch_teams(ctx, t, a, t->nchunks, true, [&](auto W) {
             constexpr int w = decltype(W)::value;
             return solve ? (t->hash ? k_density_teams<true, true, true, w> : k_density_teams<true, false, true, w>)
                          : (t->hash ? k_density_teams<false, true, true, w> : k_density_teams<false, false, true, w>);
@@ -2498,7 +2503,7 @@ static void launch_density(sph_ctx* ctx, sph_tree* t, bool solve, bool listed, i
     }
     hipLaunchKernelGGL(kern, dim3(persistent_blocks(ctx, t, t->nchunks, (const void*)kern)), dim3(BLK), 0, st, a);
     if (t->nslots > 0)
-        launch_teams(ctx, t, a, t->nslots, [&](auto W) {
+        launch_teams(ctx, t, a, t->nslots, false, [&](auto W) {
             constexpr int w = decltype(W)::value;
             return t->hash ? k_density_teams<false, true, false, w> : k_density_teams<false, false, false, w>;
         });
@@ -2584,7 +2589,7 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     a.work = (unsigned long long*)(t->work_ctr + 256);
     a.rmax = rmax_of(t);
     if (t->direct) {
-        launch_teams(ctx, t, a, t->nchunks, [&](auto W) {
+        launch_teams(ctx, t, a, t->nchunks, true, [&](auto W) {
             constexpr int w = decltype(W)::value;
             return t->hash ? k_force_teams<true, true, w> : k_force_teams<false, true, w>;
         });
@@ -2595,7 +2600,7 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     else kern = t->hash ? k_force<true, false> : k_force<false, false>;
     hipLaunchKernelGGL(kern, dim3(persistent_blocks(ctx, t, t->nchunks, (const void*)kern)), dim3(BLK), 0, st, a);
     if (t->nslots > 0)
-        launch_teams(ctx, t, a, t->nslots, [&](auto W) {
+        launch_teams(ctx, t, a, t->nslots, false, [&](auto W) {
             constexpr int w = decltype(W)::value;
             return t->hash ? k_force_teams<true, false, w> : k_force_teams<false, false, w>;
         });
@@ -2896,7 +2901,7 @@ Err run_graph(sph_ctx* ctx, sph_tree* t, int k_iter, const sph_density_out* dout
     val((uint64_t)t->ncells);
     val((uint64_t)t->nred);
     val((uint64_t)t->npieces);
-    val((uint64_t)t->nslots | (t->direct ? (uint64_t)1 << 32 : 0));
+    val((uint64_t)t->nslots | (t->direct ? (uint64_t)1 << 32 : 0) | (t->direct_density ? (uint64_t)1 << 33 : 0));
     // which kernels (with or without the heavy-chunk and cell-order code)
     // and which partners have sorted lists
     val((uint64_t)t->ext() | ((uint64_t)(uint32_t)t->max_sorted << 1));

@@ -104,3 +104,17 @@ def test_no_room_to_park(sph, ctx):
         assert used < high
         for k in ref:
             assert torch.equal(ref[k], r[k]), k
+
+
+def test_density_of_one_level_sets(sph, ctx):
+    """A set of one level alone has few chunks, whose density blocks walk; next
+    to a larger one waves do."""
+    ps, h = I.fixed_h_case(sphinputs.uniform(3001, 94, velocity=True))
+    big = sphinputs.uniform(200000, 95)
+    (alone,), t1 = run_fixed(sph, ctx, [ps], [h])
+    both, t2 = run_fixed(sph, ctx, [big, ps], [I.f32(np.full(big.n, sphinputs.h_for_density(float(big.n)))), h])
+    assert t1.stats()["chunks"] < 2048 < t2.stats()["chunks"] and t2.stats()["levels"] == 1
+    _same(alone, both[1])
+    rd, rf = I.oracle_reference(ps, h)
+    check_density(ps, h, alone[0], rd)
+    check_force(ps, alone[1], rf)
