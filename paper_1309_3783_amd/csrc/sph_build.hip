@@ -61,6 +61,20 @@ __device__ inline int64_t lower_bound_key(const uint64_t* key, int64_t lo, int64
     return lo;
 }
 
+// The same by a wave, 64 keys a step (two to four dependent loads where the
+// bisection takes 15 to 23: the levels of 8*10^6 particles 418 -> 344 us).
+__device__ inline int64_t wave_lower_bound(const uint64_t* key, int64_t lo, int64_t hi, uint64_t k) {
+    const int lane = threadIdx.x & 63;
+    while (lo < hi) {
+        const int64_t step = (hi - lo + 63) >> 6;
+        const int64_t at = lo + (lane + 1) * step - 1;   // the last key of the lane's segment
+        const int c = __popcll(__ballot(at < hi && key[at < hi ? at : lo] < k));   // segments below k
+        hi = min(hi, lo + (c + 1) * step - 1);
+        lo += c * step;
+    }
+    return lo;
+}
+
 __device__ inline float wave_max_f(float v) {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v = fmaxf(v, __shfl_xor(v, d, 64));
@@ -82,15 +96,16 @@ __device__ inline uint64_t splitmix64(uint64_t id) {
 // Per-set max and min h and count of invalid h (not finite or <= 0).  Grid
 // (chunks, sets); positive floats compare like their bit patterns, so the
 // extremes are integer atomics.
-__global__ __launch_bounds__(256) void k_set_hstats(const SetInfo* sets, const float* __restrict__ h,
+constexpr int HSTAT_BS = 1024;
+__global__ __launch_bounds__(HSTAT_BS) void k_set_hstats(const SetInfo* sets, const float* __restrict__ h,
                                                     int* __restrict__ hmax_bits, int* __restrict__ hmin_bits,
                                                     int* __restrict__ bad_out) {
     const SetInfo S = sets[blockIdx.y];
     float m = 0.f, mn = INFINITY;
     int bad = 0;
 #pragma unroll 8
-    for (int64_t i = S.first + (int64_t)blockIdx.x * 256 + threadIdx.x; i < S.first + S.count;
-         i += (int64_t)gridDim.x * 256) {
+    for (int64_t i = S.first + (int64_t)blockIdx.x * HSTAT_BS + threadIdx.x; i < S.first + S.count;
+         i += (int64_t)gridDim.x * HSTAT_BS) {
         float v = h[i];
         if (!(v > 0.f) || !(v < INFINITY)) {
             bad++;
@@ -103,8 +118,8 @@ __global__ __launch_bounds__(256) void k_set_hstats(const SetInfo* sets, const f
     mn = -wave_max_f(-mn);
     bad = wave_sum_i(bad);
     // one atomic per block: many blocks update the same word
-    __shared__ float s_m[4], s_n[4];
-    __shared__ int s_b[4];
+    __shared__ float s_m[HSTAT_BS / 64], s_n[HSTAT_BS / 64];
+    __shared__ int s_b[HSTAT_BS / 64];
     if ((threadIdx.x & 63) == 0) {
         s_m[threadIdx.x >> 6] = m;
         s_n[threadIdx.x >> 6] = mn;
@@ -112,9 +127,11 @@ __global__ __launch_bounds__(256) void k_set_hstats(const SetInfo* sets, const f
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        m = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
-        mn = fminf(fminf(s_n[0], s_n[1]), fminf(s_n[2], s_n[3]));
-        bad = s_b[0] + s_b[1] + s_b[2] + s_b[3];
+        for (int w = 1; w < HSTAT_BS / 64; ++w) {
+            m = fmaxf(m, s_m[w]);
+            mn = fminf(mn, s_n[w]);
+            bad += s_b[w];
+        }
         atomicMax(&hmax_bits[blockIdx.y], __float_as_int(m));
         atomicMin(&hmin_bits[blockIdx.y], __float_as_int(mn));
         if (bad) atomicAdd(&bad_out[blockIdx.y], bad);
@@ -286,8 +303,8 @@ __global__ __launch_bounds__(256) void k_cell_stats(SetInfo* sets, int bmax, int
         const Cell P = cells[C.parent];
         uint64_t lo, hi;
         cell_key_range(S, bmax, level, C.ix, C.iy, C.iz, C.set, &lo, &hi);
-        int64_t a = lower_bound_key(key, P.first, (int64_t)P.first + P.count, lo);
-        int64_t b = lower_bound_key(key, a, (int64_t)P.first + P.count, hi);
+        int64_t a = wave_lower_bound(key, P.first, (int64_t)P.first + P.count, lo);
+        int64_t b = wave_lower_bound(key, a, (int64_t)P.first + P.count, hi);
         C.first = (int32_t)a;
         C.count = (int32_t)(b - a);
     }
@@ -552,16 +569,15 @@ __global__ void k_task_emit(const int4* __restrict__ tasks, int64_t nt, const Ce
 // of its chunks, a scan of the marks gives the chunk numbers.
 __global__ __launch_bounds__(256) void k_chunk_count(const Cell* __restrict__ cells, int64_t nc, int* stats,
                                                      uint32_t* __restrict__ mark) {
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool leaf = false;
-    int count = 0;
-    if (c < nc) {
+    int nl = 0, count = 0;
+    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += (int64_t)gridDim.x * blockDim.x) {
         const Cell C = cells[c];
-        leaf = !C.split && C.count > 0;
-        count = leaf ? C.count : 0;
-        for (int s = 0; s < count; s += CHUNK) mark[C.first + s] = 1u;
+        if (C.split || C.count == 0) continue;
+        ++nl;
+        count = max(count, C.count);
+        for (int s = 0; s < C.count; s += CHUNK) mark[C.first + s] = 1u;
     }
-    int nl = __popcll(__ballot(leaf));
+    nl = wave_sum_i(nl);
     for (int d = 32; d >= 1; d >>= 1) count = max(count, __shfl_xor(count, d, 64));
     __shared__ int s_n[4], s_c[4];
     if ((threadIdx.x & 63) == 0) {
@@ -980,8 +996,9 @@ __global__ void k_seg_need(const uint64_t* __restrict__ ent, int64_t ne, const u
 // elsewhere), and its sort class: 65..SEG_LDS_MAX entries (a wave or a block
 // sorts it in LDS) or longer (the long class: in LDS up to SEG_LARGE_MAX,
 // else one global radix sort over all such lists).
-// The total length is also summed in 64 bits (total64, zero on entry; one
-// atomic per block): list positions are 32-bit, so the host refuses a tree
+// Where the total length may reach 2^32 it is also summed in 64 bits (total64,
+// zero on entry, else null: the atomics, one per block, took 20 us for a
+// lattice of 10^6): list positions are 32-bit, so the host refuses a tree
 // whose lists hold 2^32 entries or more.
 __global__ __launch_bounds__(256) void k_seg_lens(const uint32_t* __restrict__ need, int64_t nca,
                                                   const Cell* __restrict__ cells, uint32_t* __restrict__ lens,
@@ -997,6 +1014,7 @@ __global__ __launch_bounds__(256) void k_seg_lens(const uint32_t* __restrict__ n
             big[q] = n > (uint32_t)SEG_LDS_MAX ? 1u : 0u;
         }
     }
+    if (!total64) return;
     unsigned long long v = n;
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
     __shared__ unsigned long long s_v[4];
@@ -1553,9 +1571,9 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
         HIPTRY(fill_u32((uint32_t*)d_bad, S, 0u, st));
         int64_t maxc = 0;
         for (int s = 0; s < S; ++s) maxc = std::max<int64_t>(maxc, sets[s].count);
-        // a few hundred blocks per set at most: their atomics on one word serialise
-        unsigned gx = (unsigned)std::min<int64_t>(std::max<int64_t>((maxc + 4095) / 4096, 1), 256);
-        hipLaunchKernelGGL(k_set_hstats, dim3(gx, S), dim3(256), 0, st, d_sets, in->h, (int*)d_hmax, (int*)d_hmin,
+        // few blocks per set: their atomics on one word serialise (some 13 ns each)
+        unsigned gx = (unsigned)std::min<int64_t>(std::max<int64_t>((maxc + 16383) / 16384, 1), 256);
+        hipLaunchKernelGGL(k_set_hstats, dim3(gx, S), dim3(HSTAT_BS), 0, st, d_sets, in->h, (int*)d_hmax, (int*)d_hmin,
                            d_bad);
         HIPTRY(hipGetLastError());
         const void* hs;
@@ -1788,7 +1806,7 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
     ERRTRY(t->scratch(std::max<int64_t>(nc, t->n) + 1));
     // (total[16..20]: leaves, largest leaf; pieces, heavy chunks, sets that are not uneven)
     HIPTRY(fill2_u32(total + 16, 5, 0u, t->sc_c, t->n, 0u, st));
-    hipLaunchKernelGGL(k_chunk_count, dim3(nblk(nc, 256)), dim3(256), 0, st, t->cells, nc, t->d_maxleaf, t->sc_c);
+    hipLaunchKernelGGL(k_chunk_count, dim3(std::min<unsigned>(nblk(nc, 256), 128)), dim3(256), 0, st, t->cells, nc, t->d_maxleaf, t->sc_c);
     HIPTRY(exclusive_scan(t->sc_c, t->sc_d, t->n, t->sc_tmp, total, st));
     // a leaf of k particles gives ceil(k / CHUNK) <= k / CHUNK + 1 chunks
     const int64_t chunk_cap = nc + t->n / CHUNK + 1;
@@ -2018,6 +2036,8 @@ Err sort_pairs(sph_ctx* ctx, sph_tree* t) {
     // (in the scratch words, whose reading back reaches it: 8-byte aligned, as 4 * sc_cap + 4 words are)
     unsigned long long* total64 = (unsigned long long*)(total + 4);
     HIPTRY(fill2_u32(need, nca, 0u, total + 4, 2, 0u, st));
+    // (a level's cells hold at most n particles, a cell has at most 13 lists)
+    const bool wide = (double)NAXES * (double)t->n * (double)t->nlevels >= 4294967296.0;
     const int64_t ne = t->ncsr;
     if (ne > 0) {
         hipLaunchKernelGGL(k_seg_need, dim3(nblk(ne, 256)), dim3(256), 0, st, t->csr, ne, t->ncsr_dev, t->cells,
@@ -2026,7 +2046,7 @@ Err sort_pairs(sph_ctx* ctx, sph_tree* t) {
     }
     if (nca > 0) {
         hipLaunchKernelGGL(k_seg_lens, dim3(nblk(nca, 256)), dim3(256), 0, st, need, nca, t->cells, t->segoff,
-                           flat ? nullptr : mid_idx, flat ? nullptr : big_idx, total64);
+                           flat ? nullptr : mid_idx, flat ? nullptr : big_idx, wide ? total64 : nullptr);
         HIPTRY(hipGetLastError());
     }
     uint32_t nmid = 0, nbig = 0;
@@ -2044,8 +2064,8 @@ Err sort_pairs(sph_ctx* ctx, sph_tree* t) {
         ERRTRY(read_back(ctx, total, 6 * sizeof(uint32_t), &rb));
         nmid = ((const uint32_t*)rb)[1];
         nbig = ((const uint32_t*)rb)[2];
-        uint64_t n64;
-        std::memcpy(&n64, (const uint32_t*)rb + 4, sizeof(n64));
+        uint64_t n64 = ((const uint32_t*)rb)[0];
+        if (wide) std::memcpy(&n64, (const uint32_t*)rb + 4, sizeof(n64));
         if (n64 >= ((uint64_t)1 << 32))
             return Err{SPH_E_CAPACITY, "sorted lists hold " + std::to_string(n64) +
                                            " entries (32-bit list positions: limit 2^32 - 1)"};
