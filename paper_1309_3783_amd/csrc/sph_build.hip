@@ -53,16 +53,9 @@ __device__ inline int set_of_top(const SetInfo* sets, int nsets, int c) {
     return lo;
 }
 
-__device__ inline int64_t lower_bound_key(const uint64_t* key, int64_t lo, int64_t hi, uint64_t k) {
-    while (lo < hi) {
-        int64_t mid = lo + ((hi - lo) >> 1);
-        if (key[mid] < k) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
-// The same by a wave, 64 keys a step (two to four dependent loads where the
-// bisection takes 15 to 23: the levels of 8*10^6 particles 418 -> 344 us).
+// The first key in [lo, hi) not below k, by a wave, 64 keys a step (two to four
+// dependent loads where a bisection takes 15 to 23: the levels of 8*10^6
+// particles 418 -> 344 us).
 __device__ inline int64_t wave_lower_bound(const uint64_t* key, int64_t lo, int64_t hi, uint64_t k) {
     const int lane = threadIdx.x & 63;
     while (lo < hi) {
@@ -162,8 +155,10 @@ __global__ void k_keys(const SetInfo* sets, int nsets, int64_t n, const double* 
                        const double* __restrict__ y, const double* __restrict__ z, const float* __restrict__ h,
                        const float* __restrict__ m, const float* __restrict__ u, const float* __restrict__ vx,
                        const float* __restrict__ vy, const float* __restrict__ vz, int bmax,
-                       uint64_t* __restrict__ key, uint32_t* __restrict__ val, InRec* __restrict__ rec) {
+                       uint64_t* __restrict__ key, uint32_t* __restrict__ val, InRec* __restrict__ rec,
+                       uint32_t* __restrict__ top_end, int ntop) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t c = i; c < ntop; c += (int64_t)gridDim.x * blockDim.x) top_end[c] = 0;   // (for k_gather)
     if (i >= n) return;
     int s = set_of_particle(sets, nsets, i);
     const SetInfo S = sets[s];
@@ -213,12 +208,21 @@ __global__ void k_gather(const SetInfo* sets, int nsets, int64_t n, int bmax,
                          const InRec* __restrict__ rec, float slack, float4* __restrict__ pos,
                          float4* __restrict__ plo, float* __restrict__ ph, float* __restrict__ hdec, float* __restrict__ pu,
                          float4* __restrict__ pv, uint32_t* __restrict__ perm, uint32_t* __restrict__ iperm,
-                         uint64_t* __restrict__ mix) {
+                         uint64_t* __restrict__ mix, uint32_t* __restrict__ top_first,
+                         uint32_t* __restrict__ top_end) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     uint32_t i = val[p];
-    int s = nsets > 1 ? (int)(key[p] >> (3 * bmax)) : 0;
+    const uint64_t kp = key[p];
+    int s = nsets > 1 ? (int)(kp >> (3 * bmax)) : 0;
     const SetInfo S = sets[s];
+    // where the particle's top cell starts and ends (the bits above its
+    // levels: set and top cell)
+    const int sh = S.key_shift + 3 * S.depth;
+    const uint64_t t = kp >> sh;
+    const int c = S.top_base + (int)(t & ((1ull << (3 * S.lgG)) - 1ull));
+    if (p == 0 || key[p - 1] >> sh != t) top_first[c] = (uint32_t)p;
+    if (p == n - 1 || key[p + 1] >> sh != t) top_end[c] = (uint32_t)p + 1u;
     int64_t R = (int64_t)1 << (S.lgG + S.depth);
     const InRec r = rec[i];
     double xs[3] = {r.x, r.y, r.z};
@@ -254,8 +258,9 @@ __device__ inline void cell_key_range(const SetInfo& S, int bmax, int level, int
     *hi = *lo + (1ull << sh);
 }
 
-__global__ void k_top_cells(const SetInfo* sets, int nsets, int ntop, int bmax,
-                            const uint64_t* __restrict__ key, Cell* __restrict__ cells) {
+__global__ void k_top_cells(const SetInfo* sets, int nsets, int ntop,
+                            const uint32_t* __restrict__ top_first, const uint32_t* __restrict__ top_end,
+                            Cell* __restrict__ cells) {
     int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ntop) return;
     int s = set_of_top(sets, nsets, c);
@@ -269,12 +274,9 @@ __global__ void k_top_cells(const SetInfo* sets, int nsets, int ntop, int bmax,
     C.set = (int16_t)s;
     C.parent = -1;
     C.child = -1;
-    uint64_t lo, hi;
-    cell_key_range(S, bmax, 0, C.ix, C.iy, C.iz, s, &lo, &hi);
-    int64_t a = lower_bound_key(key, S.first, S.first + S.count, lo);
-    int64_t b = lower_bound_key(key, a, S.first + S.count, hi);
-    C.first = (int32_t)a;
-    C.count = (int32_t)(b - a);
+    const uint32_t end = top_end[c];   // (0: no particles)
+    C.first = end ? (int32_t)top_first[c] : 0;
+    C.count = (int32_t)end - C.first;
     C.hmax = 0.f;
     C.hcur = 0.f;
     C.hcur_l = 0.f;
@@ -1659,9 +1661,14 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
                     (void**)&t->rs_tmp));
     InRec* rec;
     ERRTRY(t->alloc(t->b_inrec, sizeof(InRec) * nn, (void**)&rec));
+    // first and last particles of the top cells, noted by the gather
+    ERRTRY(t->scratch(ntop + 1));
+    uint32_t *top_first = t->sc_c, *top_end = t->sc_d;
+    if (n == 0) HIPTRY(fill_u32(top_end, ntop, 0u, st));
     if (n > 0) {
         hipLaunchKernelGGL(k_keys, dim3(nblk(n, 256)), dim3(256), 0, st, d_sets, S, n, in->x, in->y, in->z, in->h,
-                           in->m, in->u, in->vx, in->vy, in->vz, bmax, t->key2, t->val2, rec);
+                           in->m, in->u, in->vx, in->vy, in->vz, bmax, t->key2, t->val2, rec, top_end,
+                           (int)ntop);
         HIPTRY(hipGetLastError());
         bool alt = false;
         HIPTRY(radix_sort(t->key2, t->val2, t->key, t->val, n, t->key_bits, t->rs_tmp, st, &alt));
@@ -1673,7 +1680,7 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
         }
         hipLaunchKernelGGL(k_gather, dim3(nblk(n, 256)), dim3(256), 0, st, d_sets, S, n, bmax, t->key,
                            t->val, rec, prm->h_slack, t->pos, t->plo, t->ph, t->hdec, t->pu, t->pv, t->perm,
-                           t->iperm, t->mix);
+                           t->iperm, t->mix, top_first, top_end);
         HIPTRY(hipGetLastError());
     }
 
@@ -1683,11 +1690,10 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
     ERRTRY(t->alloc(t->b_cell, sizeof(Cell) * cap_cells, (void**)&t->cells));
     t->lvl_start.assign(1, 0);
     t->lvl_start.push_back(ntop);
-    hipLaunchKernelGGL(k_top_cells, dim3(nblk(ntop, 256)), dim3(256), 0, st, d_sets, S, (int)ntop, bmax, t->key,
+    hipLaunchKernelGGL(k_top_cells, dim3(nblk(ntop, 256)), dim3(256), 0, st, d_sets, S, (int)ntop, top_first, top_end,
                        t->cells);
     HIPTRY(hipGetLastError());
     // top-level tasks and the split flags of level 0: one read-back for both
-    ERRTRY(t->scratch(ntop + 1));
     ERRTRY(t->alloc(t->b_split, sizeof(uint32_t) * (ntop + 1), (void**)&t->split_idx));
     hipLaunchKernelGGL(k_cell_stats, dim3(nblk(ntop, 4)), dim3(256), 0, st, d_sets, bmax, 0, (int64_t)0,
                        ntop, t->key, t->hdec, prm->n_split, prm->split_frac, t->cells, t->split_idx);
