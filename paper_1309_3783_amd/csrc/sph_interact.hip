@@ -722,13 +722,15 @@ __device__ __forceinline__ int skip_blocks(const float4* __restrict__ blkbox, co
 // walk ends with bitwise the same results.  This needs every sum to be added
 // up tile by tile: force chunks of sets whose du and S run on in FP32 (sets
 // of one level, see ForceP::fold) are never parked.
+//
 // The tiles that a walk goes on for, and those from which it is taken for a
 // long one: with fewer, walks about to end take up the slots and the time of
-// the second kernel (100 sets of 27685, 7% of the passes after the first),
-// with more, the longest go on alone for longer (a set of 10^6, density and
-// force: 5.6 ms with 24 and 48, 6.6 with 64 and 96, 9.2 without parking).
-// The counters are not read before the walk is about that long: the loads
-// from all waves cost the density passes over 8 * 10^6 particles 10%.
+// the second kernel (a graph of 100 sets of 4037: 4.49 ms with 24 and 32, 4.37
+// with 24 and 64), with more, the longest go on alone for longer (a set of
+// 10^6, build, density and force: 5.6 ms with 24 and 48, 6.6 with 64 and 96, 9.2
+// without parking).  The counters are not read before the walk is about that
+// long: the loads from all waves cost the density passes over 8 * 10^6 particles
+// 10%.
 constexpr int GRACE = 24;
 constexpr int PARK_MIN = 48;
 
@@ -2039,8 +2041,8 @@ __global__ __launch_bounds__(COUNT_BS) void k_count_final(const int4* __restrict
 // block per chunk adds its particles still active to its set's count, and the
 // last block to end writes the counts to status and clears them.  A pass over
 // 10^4 particles takes 20 to 100 us, the launches for step and counts 14 us, one
-// of these 6; with more blocks their atomics on one word take longer than the
-// launches (3906 blocks: 130 us).
+// of these 6; with more blocks their atomics on one word, some 13 ns each, take
+// longer than the launches.
 constexpr int NEWTON_BLOCKS = 64, NEWTON_BS = 512;
 __global__ __launch_bounds__(NEWTON_BS) void k_newton_count(const int4* __restrict__ red, Zero z,
                                                             const SetInfo* __restrict__ sets, int nsets,
@@ -2335,10 +2337,12 @@ static Err ensure_state(const sph_ctx* ctx, sph_tree* t) {
     t->fvs = t->fdu + n;
     t->fS = t->fvs + n;
     t->fn = (int32_t*)(t->fS + n);
-    // who walks the chunks (see walk): teams from the start where every set is
-    // uneven and there are no more chunks than waves fit; else waves, with slots
-    // for the walks they park, where the tree has long walks at all.  More than PARK_SLOTS
-    // walks (eight per CU) parked at a time would be no tail.
+    // who walks the chunks (see walk): blocks from the start where every set is
+    // uneven and there are no more chunks than waves fit (200000 particles, 4819
+    // chunks: the h solve and force 5.0 ms by blocks, 5.8 by waves that park their
+    // long walks); else waves, with slots for the walks they park, where the
+    // tree has long walks at all.  More than PARK_SLOTS walks (eight per CU)
+    // parked at a time would be no tail.
     t->direct = t->ext() && t->nplain == 0 && t->npieces == 0 && t->nchunks <= 20 * (int64_t)ctx->n_cu;
     // The density sums of a set of one level are added up tile by tile too, so
     // blocks walk a few chunks of those (16927 particles, 512 chunks: the h
@@ -2454,9 +2458,9 @@ static DensArgs dens_args(sph_tree* t, int* counter, const int* lcount) {
 // blocks per CU that fit at once taking them in turn, 3.5 with a block each).
 // Parked walks, of which most passes have few: two blocks per CU take them
 // in turn.  Eight waves a block where that leaves blocks idle otherwise (30011
-// particles, 597 chunks: 1.05 ms for the whole pass over density and force
-// against 1.12 with four and 1.15 with sixteen), four where the chunks are
-// more than fit (200000 particles: 3.5 against 4.2 ms with two).
+// particles, 597 chunks: 0.90 ms for build, density and force against 0.99 with
+// four; sixteen were slower too), four where the chunks are more than fit
+// (200000 particles: 3.5 against 4.2 ms with two).
 template <class A, class F>
 static void launch_teams(const sph_ctx* ctx, const sph_tree* t, const A& a, int64_t items, bool chunks, F kern) {
     const bool wide = items <= 4 * (int64_t)ctx->n_cu || !chunks;
