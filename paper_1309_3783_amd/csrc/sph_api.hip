@@ -125,13 +125,13 @@ sph_status sph_ctx_create(sph_ctx** out, int device, void* stream) {
         delete c;
         return SPH_E_WORKSPACE;
     }
-    if (hipHostMalloc(&c->h_pin, sph_ctx::PIN_BYTES, hipHostMallocCoherent) != hipSuccess) {
+    if (hipHostMalloc(&c->h_pin, sph_ctx::PIN_ALL, hipHostMallocCoherent) != hipSuccess) {
         c->h_pin = nullptr;
         (void)hipFree(c->d_counter);
         delete c;
         return SPH_E_WORKSPACE;
     }
-    std::memset(c->h_pin, 0, sph_ctx::PIN_BYTES);
+    std::memset(c->h_pin, 0, sph_ctx::PIN_ALL);
     *out = c;
     return SPH_OK;
 }

@@ -1477,14 +1477,10 @@ __global__ __launch_bounds__(256) void k_publish(const uint32_t* __restrict__ sr
 }
 
 static Err read_back(sph_ctx* ctx, const void* d, size_t bytes, const void** h) {
-    if (bytes > sph_ctx::PIN_BYTES) return Err{SPH_E_STATE, "internal: read-back larger than the pinned buffer"};
+    if (bytes > sph_ctx::PIN_BYTES || bytes % sizeof(uint32_t))
+        return Err{SPH_E_STATE, "internal: read-back larger than the pinned buffer"};
     uint32_t* done = (uint32_t*)((char*)ctx->h_pin + sph_ctx::PIN_DONE);
     *h = ctx->h_pin;
-    if (bytes > sph_ctx::PIN_SOLVE || bytes % sizeof(uint32_t)) {
-        HIPTRY(hipMemcpyAsync(ctx->h_pin, d, bytes, hipMemcpyDeviceToHost, ctx->stream));
-        HIPTRY(hipStreamSynchronize(ctx->stream));
-        return Err{};
-    }
     const uint32_t seq = ctx->next_seq();
     hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, ctx->stream, (const uint32_t*)d,
                        (int)(bytes / sizeof(uint32_t)), (uint32_t*)ctx->h_pin, done, seq);

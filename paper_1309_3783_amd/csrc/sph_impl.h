@@ -42,9 +42,11 @@ struct sph_ctx {
     // by its number (pin_seq, never zero) which the host waits for: at PIN_DONE
     // for those read back, in each of the two slots of the Newton loop's
     // status words at PIN_SOLVE
+    // (behind the PIN_BYTES that a read-back may take)
     static constexpr size_t PIN_BYTES = 65536;
-    static constexpr size_t PIN_SOLVE = 32768;
-    static constexpr size_t PIN_DONE = 49152;
+    static constexpr size_t PIN_SOLVE = PIN_BYTES;
+    static constexpr size_t PIN_DONE = PIN_BYTES + 256;
+    static constexpr size_t PIN_ALL = PIN_BYTES + 512;
     void* h_pin = nullptr;
     uint32_t pin_seq = 0;
     uint32_t next_seq() { return ++pin_seq ? pin_seq : ++pin_seq; }

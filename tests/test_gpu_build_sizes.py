@@ -67,3 +67,24 @@ def test_newton_counts(sph, max_iter):
     assert left65 == left64 + left1
     assert (left65 > 0) == (max_iter == 3)
 
+
+
+def test_counts_of_many_sets(sph):
+    """The h extremes of 3000 sets are read back in one piece (36 KB)."""
+    few = [sphinputs.uniform(120 + k % 3, 700 + k) for k in range(6)]
+    prm = sph.params(h_slack=1.0, max_iter=3)
+
+    def solve(sets):
+        batch = sph.batch_from_sets(sets)
+        tree = sph.Tree(sph.Context(0))
+        for _ in range(2):
+            tree.build_cells(batch, prm, h=None)
+            tree.sort_pairs()
+            out = sph.DensityOut(batch.n, "cuda")
+            tree.density(out)
+        torch.cuda.synchronize()
+        return out.rho.cpu().numpy(), out.nngb.cpu().numpy()
+
+    r1, n1 = solve(few)
+    r2, n2 = solve(few * 500)
+    assert np.array_equal(np.tile(r1, 500), r2) and np.array_equal(np.tile(n1, 500), n2)
