@@ -279,6 +279,7 @@ struct sph_tree {
             m->cap = 0;
         }
         if (ws) ar.reset(ar.base, ar.cap);
+        drop_scratch_views();
         pcost = nullptr;
         order = nullptr;
         nslots = 0;
@@ -464,11 +465,18 @@ struct sph_tree {
     }
 
     // four uint32 scratch arrays of n entries plus scan scratch and counters
+    // (kept while they are large enough: the views must not outlive the block)
+    void drop_scratch_views() {
+        sc_a = sc_b = sc_c = sc_d = sc_tmp = d_total = nullptr;
+        d_maxleaf = d_npairs = nullptr;
+        sc_cap = 0;
+    }
     sph::Err scratch(int64_t n) {
         n = std::max<int64_t>(n, 1);
         if (n <= sc_cap && sc_a) return sph::Err{};
         int64_t cap = std::max<int64_t>(n, sc_cap * 3 / 2);
         size_t words = 4 * (size_t)cap + sph::SCAN_JOBS * sph::scan_tmp_words(cap) + 64;
+        drop_scratch_views();   // (a failed allocation has given the old block back)
         void* p;
         sph::Err e = alloc(b_sc, words * sizeof(uint32_t), &p);
         if (e.st) return e;
