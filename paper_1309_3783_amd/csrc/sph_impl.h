@@ -252,6 +252,10 @@ struct sph_tree {
         gkey.clear();
     }
 
+    // the reduction table is that of the sets, and its block is still held (one
+    // that failed to grow was given back)
+    bool red_made() const { return b_red.p && red_off == off; }
+
     size_t bytes() const {
         size_t b = 0;
         for (const sph::DevBuf* d : bufs()) b += d->cap;

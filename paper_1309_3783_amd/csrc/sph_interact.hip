@@ -2352,7 +2352,8 @@ static Err ensure_state(const sph_ctx* ctx, sph_tree* t) {
     t->nslots = t->ext() && !t->direct ? std::min<int64_t>(t->nchunks, PARK_SLOTS) : 0;
     if (t->nslots > 0 && !t->try_alloc(t->b_park, (size_t)PARK_BYTES * t->nslots, &p)) t->nslots = 0;
     // reduction chunks: RED_CHUNK particles of one set each
-    if (t->red_off != t->off) {
+    if (!t->red_made()) {
+        t->red_off.clear();
         t->red_chunks.clear();
         for (int s = 0; s < t->nsets; ++s) {
             int64_t a = t->off[s], b = t->off[s + 1];

@@ -46,7 +46,32 @@ static void scratch_follows_the_memory() {
     std::printf("ok scratch_follows_the_memory\n");
 }
 
+// The reduction table kept for the next call of the same sets counts only
+// while its block is held: not after it made way for one that did not fit.
+static void reduction_table_needs_its_block() {
+    const size_t MB = (size_t)1 << 20;
+    char* a = (char*)std::aligned_alloc(256, MB);
+    sph_tree t;
+    void* p = nullptr;
+    expect(!t.set_workspace(a, MB, 0).st, "attach");
+    t.off = {0, 1000};
+    expect(!t.red_made(), "none yet");
+    expect(!t.alloc(t.b_red, 1000, &p).st, "table");
+    t.red_off = t.off;
+    expect(t.red_made(), "made");
+    expect(t.alloc(t.b_red, 2 * MB, &p).st == SPH_E_WORKSPACE, "does not fit");
+    expect(!t.red_made(), "gone");
+    expect(!t.alloc(t.b_red, 1000, &p).st, "table again");
+    t.red_off = t.off;
+    t.off = {0, 500, 1000};
+    expect(!t.red_made(), "other sets");
+    t.release();
+    std::free(a);
+    std::printf("ok reduction_table_needs_its_block\n");
+}
+
 int main() {
+    reduction_table_needs_its_block();
     scratch_follows_the_memory();
     return 0;
 }
