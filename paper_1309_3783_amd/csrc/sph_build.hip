@@ -1658,6 +1658,9 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
                     (void**)&t->rs_tmp));
     InRec* rec;
     ERRTRY(t->alloc(t->b_inrec, sizeof(InRec) * nn, (void**)&rec));
+    // cells: capacity estimate; grown on demand
+    int64_t cap_cells = ntop + 8 * (n / (prm->n_split + 1) + 1) * (depth + 1) / 2 + 64;
+    ERRTRY(t->alloc(t->b_cell, sizeof(Cell) * cap_cells, (void**)&t->cells));
     // first and last particles of the top cells, noted by the gather
     ERRTRY(t->scratch(ntop + 1));
     uint32_t *top_first = t->sc_c, *top_end = t->sc_d;
@@ -1682,9 +1685,6 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
     }
 
     // ---- levels: cells and tasks ----------------------------------------
-    // capacity estimate; grown on demand
-    int64_t cap_cells = ntop + 8 * (n / (prm->n_split + 1) + 1) * (depth + 1) / 2 + 64;
-    ERRTRY(t->alloc(t->b_cell, sizeof(Cell) * cap_cells, (void**)&t->cells));
     t->lvl_start.assign(1, 0);
     t->lvl_start.push_back(ntop);
     hipLaunchKernelGGL(k_top_cells, dim3(nblk(ntop, 256)), dim3(256), 0, st, d_sets, S, (int)ntop, top_first, top_end,
@@ -1700,7 +1700,7 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
                        t->sc_a);
     {
         const ScanJob jobs[] = {{t->sc_a, t->sc_b, ntop, total}, {t->split_idx, t->split_idx, ntop, total + 2}};
-        HIPTRY(exclusive_scans(jobs, 2, t->sc_tmp, st));
+        HIPTRY(exclusive_scans(jobs, 2, t->sc_tmp, t->rs_tmp, st));
     }
     const void* rb;
     ERRTRY(read_back(ctx, total, 3 * sizeof(uint32_t), &rb));
@@ -1778,7 +1778,7 @@ Err build_tree(sph_ctx* ctx, sph_tree* t, const sph_input* in, const sph_params*
             const ScanJob jobs[] = {{t->sc_a, t->sc_b, ncur, total},
                                     {t->sc_c, t->sc_d, ncur, total + 1},
                                     {t->split_idx, t->split_idx, nnext, total + 2}};
-            HIPTRY(exclusive_scans(jobs, 3, t->sc_tmp, st));
+            HIPTRY(exclusive_scans(jobs, 3, t->sc_tmp, t->rs_tmp, st));
         }
         ERRTRY(read_back(ctx, total, 3 * sizeof(uint32_t), &rb));
         const uint32_t nf = ncur > 0 ? ((const uint32_t*)rb)[0] : 0u;
@@ -2036,6 +2036,8 @@ Err sort_pairs(sph_ctx* ctx, sph_tree* t) {
     uint32_t* need = t->sc_a;
     uint32_t* mid_idx = t->sc_c;
     uint32_t* big_idx = t->sc_d;
+    // (the scans' batch words, if a sort that ran out of memory gave them back)
+    ERRTRY(t->alloc(t->b_rs, sizeof(uint32_t) * radix_tmp_words(1 << 20), (void**)&t->rs_tmp));
     // (in the scratch words, whose reading back reaches it: 8-byte aligned, as 4 * sc_cap + 4 words are)
     unsigned long long* total64 = (unsigned long long*)(total + 4);
     HIPTRY(fill2_u32(need, nca, 0u, total + 4, 2, 0u, st));
@@ -2062,7 +2064,7 @@ Err sort_pairs(sph_ctx* ctx, sph_tree* t) {
         const ScanJob jobs[] = {{t->segoff, t->segoff, nca, total},
                                 {mid_idx, mid_idx, nca, total + 1},
                                 {big_idx, big_idx, nca, total + 2}};
-        HIPTRY(exclusive_scans(jobs, 3, t->sc_tmp, st));
+        HIPTRY(exclusive_scans(jobs, 3, t->sc_tmp, t->rs_tmp, st));
         const void* rb;
         ERRTRY(read_back(ctx, total, 6 * sizeof(uint32_t), &rb));
         nmid = ((const uint32_t*)rb)[1];

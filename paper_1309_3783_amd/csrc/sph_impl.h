@@ -67,11 +67,16 @@ Err wait_pinned(sph_ctx* ctx, const uint32_t* word, uint32_t seq, bool behind);
 // context, so a block freed by a call and reused by a later allocation is
 // written only after every earlier use of it has run -- no synchronisation,
 // no hipMalloc, no hipFree.
+// Blocks that the tree can do without are lent from the region's top: the
+// free list counts their memory as free, so that the other blocks lie where
+// they would without them, and one that reaches into lent memory takes it
+// (the caller then calls the loans in).
 struct Arena {
     char* base = nullptr;
     size_t cap = 0;
     std::map<size_t, size_t> free_;   // offset -> size
-    size_t in_use = 0, high = 0;
+    std::map<size_t, size_t> lent_;   // offset -> size, in the last free block
+    size_t in_use = 0, lent = 0, high = 0;
 
     static size_t round(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -81,8 +86,9 @@ struct Arena {
         base = (char*)a;
         cap = bytes > skip ? (bytes - skip) & ~(size_t)255 : 0;
         free_.clear();
+        lent_.clear();
         if (cap) free_[0] = cap;
-        in_use = high = 0;
+        in_use = lent = high = 0;
     }
 
     bool take(size_t bytes, size_t* off) {
@@ -95,10 +101,37 @@ struct Arena {
             free_.erase(it);
             if (rest) free_[at] = rest;
             in_use += bytes;
-            high = std::max(high, in_use);
             return true;
         }
         return false;
+    }
+    // whether a block just taken reaches into lent memory (or above some)
+    bool in_loan(size_t off, size_t bytes) const {
+        return !lent_.empty() && off + round(bytes) > lent_.begin()->first;
+    }
+    void note_high() { high = std::max(high, in_use + lent); }
+
+    // the highest place for it in the free block that ends the region
+    bool lend(size_t bytes, size_t* off) {
+        bytes = round(bytes);
+        if (free_.empty()) return false;
+        const auto last = std::prev(free_.end());
+        size_t end = cap;
+        if (last->first + last->second != end) return false;
+        for (auto it = lent_.rbegin(); it != lent_.rend(); ++it) {
+            if (end - (it->first + it->second) >= bytes) break;
+            end = it->first;
+        }
+        if (end < last->first + bytes) return false;
+        *off = end - bytes;
+        lent_[*off] = bytes;
+        lent += bytes;
+        note_high();
+        return true;
+    }
+    void call_in(size_t off) {
+        lent -= lent_.at(off);
+        lent_.erase(off);
     }
 
     void give(size_t off, size_t bytes) {
@@ -295,12 +328,8 @@ struct sph_tree {
     // A new block of at least `bytes` (want: the preferred, larger size).
     // The optional blocks (try_alloc) make room for it if they must.
     sph::Err take(size_t bytes, size_t want, void** p, size_t* got) {
-        const size_t needed = ws_needed;
         sph::Err e = take_once(bytes, want, p, got);
-        if (e.st && drop_optional()) {
-            ws_needed = needed;
-            e = take_once(bytes, bytes, p, got);
-        }
+        if (e.st && !ws && drop_optional()) e = take_once(bytes, bytes, p, got);
         return e;
     }
     sph::Err take_once(size_t bytes, size_t want, void** p, size_t* got) {
@@ -317,6 +346,8 @@ struct sph_tree {
                                                      std::to_string(ar.in_use) + " in use, " +
                                                      std::to_string(bytes) + " more requested)"};
             }
+            if (ar.in_loan(off, *got)) drop_optional();
+            ar.note_high();
             *p = ar.base + off;
             return sph::Err{};
         }
@@ -360,30 +391,31 @@ struct sph_tree {
     // alloc of a block that the tree can do without: false if there is no room
     bool try_alloc(sph::DevBuf& b, size_t bytes, void** out) {
         if (b.cap < bytes) {
-            give(b.p, b.cap);
-            b.p = nullptr;
-            b.cap = 0;
-            const size_t needed = ws_needed;
-            size_t got = 0;
-            if (take_once(bytes, bytes + bytes / 8, &b.p, &got).st) {
-                ws_needed = needed;
+            give_optional(b);
+            if (ws) {
+                size_t off;
+                if (!ar.lend(bytes, &off)) return false;
+                b.p = ar.base + off;
+                b.cap = sph::Arena::round(bytes);
+            } else if (take_once(bytes, bytes + bytes / 8, &b.p, &b.cap).st) {
+                b = sph::DevBuf{};
                 return false;
             }
-            b.cap = got;
         }
         *out = b.p;
         return true;
     }
+    void give_optional(sph::DevBuf& b) {
+        if (b.p && ws) ar.call_in((size_t)((char*)b.p - ar.base));
+        else give(b.p, b.cap);
+        b = sph::DevBuf{};
+    }
     // Give the optional blocks back: what is enqueued with them runs before
     // any use of the memory by others (see give), later launches go without.
     bool drop_optional() {
-        bool any = false;
-        for (sph::DevBuf* b : {&b_order, &b_park}) {
-            any = any || b->p;
-            give(b->p, b->cap);
-            b->p = nullptr;
-            b->cap = 0;
-        }
+        const bool any = b_order.p || b_park.p;
+        give_optional(b_order);
+        give_optional(b_park);
         pcost = nullptr;
         order = nullptr;
         nslots = 0;
@@ -479,7 +511,7 @@ struct sph_tree {
         n = std::max<int64_t>(n, 1);
         if (n <= sc_cap && sc_a) return sph::Err{};
         int64_t cap = std::max<int64_t>(n, sc_cap * 3 / 2);
-        size_t words = 4 * (size_t)cap + sph::SCAN_JOBS * sph::scan_tmp_words(cap) + 64;
+        size_t words = 4 * (size_t)cap + sph::scan_tmp_words(cap) + 64;
         drop_scratch_views();   // (a failed allocation has given the old block back)
         void* p;
         sph::Err e = alloc(b_sc, words * sizeof(uint32_t), &p);

@@ -9,8 +9,8 @@ size_t scan_tmp_words(int64_t n);
 // out[i] = sum_{k<i} in[k] (in may equal out); *total (device, nullable) = sum.
 hipError_t exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* tmp, uint32_t* total,
                           hipStream_t st);
-// Up to three such scans in the launches of one (tmp: three times the scratch
-// of the longest).
+// Up to three such scans in the launches of one (tmp: the scratch of the
+// longest; batch: SCAN_BATCH_WORDS more for several).
 struct ScanJob {
     const uint32_t* in;
     uint32_t* out;
@@ -18,7 +18,9 @@ struct ScanJob {
     uint32_t* total;
 };
 constexpr int SCAN_JOBS = 3;
-hipError_t exclusive_scans(const ScanJob* jobs, int njobs, uint32_t* tmp, hipStream_t st);
+constexpr int64_t SCAN_MID_BLOCKS = 1024;   // tiles of the longest up to which scans share launches
+constexpr int64_t SCAN_BATCH_WORDS = SCAN_JOBS * (SCAN_MID_BLOCKS + 1);
+hipError_t exclusive_scans(const ScanJob* jobs, int njobs, uint32_t* tmp, uint32_t* batch, hipStream_t st);
 
 // Words of uint32 scratch a radix sort of n elements needs.
 size_t radix_tmp_words(int64_t n);

@@ -152,7 +152,6 @@ __global__ __launch_bounds__(1024) void k_scan_small(ScanJobs a) {
 
 // Up to SCAN_MID_BLOCKS tiles: the apply step sums the partial sums of the
 // tiles before its own (two launches instead of three).
-constexpr int64_t SCAN_MID_BLOCKS = 1024;
 __global__ __launch_bounds__(SCAN_BS) void k_scan_apply_mid(ScanJobs a) {
     const ScanJob& J = a.j[blockIdx.y];
     const uint32_t* __restrict__ in = J.in;
@@ -198,7 +197,7 @@ __global__ __launch_bounds__(SCAN_BS) void k_scan_apply_mid(ScanJobs a) {
 
 size_t scan_tmp_words(int64_t n) { return (size_t)((n + SCAN_TILE - 1) / SCAN_TILE) + 1; }
 
-hipError_t exclusive_scans(const ScanJob* jobs, int njobs, uint32_t* tmp, hipStream_t st) {
+hipError_t exclusive_scans(const ScanJob* jobs, int njobs, uint32_t* tmp, uint32_t* batch, hipStream_t st) {
     ScanJobs a{};
     int64_t nmax = 0;
     for (int k = 0; k < njobs; ++k) {
@@ -213,6 +212,7 @@ hipError_t exclusive_scans(const ScanJob* jobs, int njobs, uint32_t* tmp, hipStr
     a.bsum = tmp;
     a.stride = (int64_t)scan_tmp_words(nmax);
     if (nb <= SCAN_MID_BLOCKS) {
+        if (njobs > 1) a.bsum = batch;
         const dim3 grid((unsigned)nb, (unsigned)njobs);
         hipLaunchKernelGGL(k_scan_reduce, grid, dim3(SCAN_BS), 0, st, a);
         hipLaunchKernelGGL(k_scan_apply_mid, grid, dim3(SCAN_BS), 0, st, a);
@@ -235,7 +235,7 @@ hipError_t exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_t
                           hipStream_t st) {
     if (n <= 0) return total ? fill_u32(total, 1, 0, st) : hipSuccess;
     const ScanJob j{in, out, n, total};
-    return exclusive_scans(&j, 1, tmp, st);
+    return exclusive_scans(&j, 1, tmp, nullptr, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -450,6 +450,7 @@ __global__ __launch_bounds__(RS_SBS) void k_rs_block(uint64_t* __restrict__ key,
     }
 }
 
+static_assert(256 * ((1 << 20) / RS_TILE) >= SCAN_BATCH_WORDS, "the sort scratch of 2^20 elements holds a batch's words");
 size_t radix_tmp_words(int64_t n) {
     int64_t nb = (n + RS_TILE - 1) / RS_TILE;
     return (size_t)(256 * nb) + scan_tmp_words(256 * nb) + 8;

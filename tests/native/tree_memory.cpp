@@ -3,6 +3,9 @@
 // Prints "ok <check>" per check; a failing one ends the program.
 #include <cstdio>
 #include <cstdlib>
+#include <random>
+#include <utility>
+#include <vector>
 
 #include "../../paper_1309_3783_amd/csrc/sph_impl.h"
 
@@ -70,7 +73,66 @@ static void reduction_table_needs_its_block() {
     std::printf("ok reduction_table_needs_its_block\n");
 }
 
+// The blocks that a tree can do without change nothing for the others: in
+// every workspace the same allocations succeed, at the same places, as without
+// them, and no two blocks held overlap.
+static void optional_blocks_refuse_nothing() {
+    const size_t room = (size_t)4 << 20;
+    char* a = (char*)std::aligned_alloc(256, room);
+    char* b = (char*)std::aligned_alloc(256, room);
+    std::mt19937 rng(12345);
+    auto pick = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
+    int refused = 0, dropped = 0;
+    for (int round = 0; round < 2000; ++round) {
+        sph_tree with, without;
+        const size_t bytes = (size_t)pick(1 << 20, (int)room);
+        expect(!with.set_workspace(a, bytes, 0).st && !without.set_workspace(b, bytes, 0).st, "attach");
+        sph::DevBuf sph_tree::*bufs[] = {&sph_tree::b_key, &sph_tree::b_pos, &sph_tree::b_cell, &sph_tree::b_sc,
+                                         &sph_tree::b_plist, &sph_tree::b_part, &sph_tree::b_red, &sph_tree::b_force};
+        const int scale = pick(100, (int)(bytes / 3));
+        for (int step = 0; step < 60; ++step) {
+            void *p = nullptr, *q = nullptr;
+            if (pick(0, 3) == 0) {
+                sph::DevBuf& opt = pick(0, 1) ? with.b_order : with.b_park;
+                const bool ok = with.try_alloc(opt, (size_t)pick(1, scale), &p);
+                expect(!ok || p == opt.p, "optional block");
+            } else {
+                auto m = bufs[pick(0, 7)];
+                const size_t want = (size_t)pick(1, scale);
+                const bool held = with.b_order.p || with.b_park.p;
+                const bool grows = pick(0, 4) == 0;
+                const sph::Err e1 = grows ? with.grow(with.*m, 0, want, &p) : with.alloc(with.*m, want, &p);
+                const sph::Err e2 = grows ? without.grow(without.*m, 0, want, &q) : without.alloc(without.*m, want, &q);
+                expect(e1.st == e2.st, "refused with optional blocks only");
+                expect(e1.st || (char*)p - a == (char*)q - b, "place");
+                expect((with.*m).cap == (without.*m).cap && with.ws_needed == without.ws_needed, "size");
+                refused += e1.st ? 1 : 0;
+                dropped += held && !with.b_order.p && !with.b_park.p ? 1 : 0;
+            }
+            std::vector<std::pair<char*, size_t>> at;
+            size_t sum = 0;
+            for (const sph::DevBuf* d : with.bufs())
+                if (d->p) {
+                    at.emplace_back((char*)d->p, d->cap);
+                    sum += d->cap;
+                }
+            std::sort(at.begin(), at.end());
+            for (size_t k = 0; k < at.size(); ++k)
+                expect(at[k].first >= a && at[k].first + at[k].second <= (k + 1 < at.size() ? at[k + 1].first : a + bytes),
+                       "overlap");
+            expect(with.bytes() == sum && with.ar.high >= sum, "held");
+        }
+        with.drop_optional();
+        expect(with.ar.in_use == without.ar.in_use && with.ar.free_ == without.ar.free_, "free");
+    }
+    expect(refused > 500 && dropped > 500, "both met");
+    std::free(a);
+    std::free(b);
+    std::printf("ok optional_blocks_refuse_nothing\n");
+}
+
 int main() {
+    optional_blocks_refuse_nothing();
     reduction_table_needs_its_block();
     scratch_follows_the_memory();
     return 0;

@@ -20,7 +20,8 @@ def output(tmp_path_factory):
     return r.returncode, r.stdout + r.stderr
 
 
-@pytest.mark.parametrize("check", ["scratch_follows_the_memory", "reduction_table_needs_its_block"])
+@pytest.mark.parametrize("check", ["scratch_follows_the_memory", "reduction_table_needs_its_block",
+                                   "optional_blocks_refuse_nothing"])
 def test_tree_memory(output, check):
     rc, out = output
     assert f"ok {check}\n" in out, (rc, out)
