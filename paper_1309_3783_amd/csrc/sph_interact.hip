@@ -2061,8 +2061,7 @@ __global__ __launch_bounds__(NEWTON_BS) void k_newton_count(const int4* __restri
         bool rebuild = false;
         c += newton_step(p, active, nw, dnw, ph, bound, lo, hi, dstep, target, tol, hcap, rebuild) ? 1 : 0;
         if (rebuild) {
-            int old = atomicExch(&status[0], 1);   // (set before the block is done, as the count below)
-            asm volatile("" : "+v"(old) : : "memory");
+            atomicExch(&status[0], 1);
             atomicExch(&status[2 + 2 * R.x], 1);
         }
     }
@@ -2073,10 +2072,9 @@ __global__ __launch_bounds__(NEWTON_BS) void k_newton_count(const int4* __restri
     if (threadIdx.x == 0) {
         c = 0;
         for (int k = 0; k < NEWTON_BS / 64; ++k) c += s_c[k];
-        // (the count is added before the block is done: its old value is waited for)
-        int old = atomicAdd(&cnt[R.x], c);
-        asm volatile("" : "+v"(old) : : "memory");
-        s_last = atomicAdd(done, old < 0 ? 0 : 1) == (int)gridDim.x - 1 ? 1 : 0;
+        atomicAdd(&cnt[R.x], c);
+        // (released: the last block sees every block's counts and flags)
+        s_last = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
     }
     __syncthreads();
     if (!s_last) return;
