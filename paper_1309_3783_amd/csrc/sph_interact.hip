@@ -1799,8 +1799,8 @@ __global__ __launch_bounds__(256) void k_force_pieces(ForceArgs a) {
     if (lane >= ch.z) return;
     const int p = ch.y + lane;
     if (a.owned && a.owned[p] == 0) return;
-    double tx = 0.0, ty = 0.0, tz = 0.0;
-    float du = 0.f, vs = 0.f, Ss = 0.f;
+    double tx = 0.0, ty = 0.0, tz = 0.0, du = 0.0, Ss = 0.0;
+    float vs = 0.f;
     int nn = 0;
     uint64_t hs = 0;
     for (int k = 0; k < pn; ++k) {
@@ -1808,18 +1808,18 @@ __global__ __launch_bounds__(256) void k_force_pieces(ForceArgs a) {
         tx += q[0 * CHUNK];
         ty += q[1 * CHUNK];
         tz += q[2 * CHUNK];
-        du += (float)q[3 * CHUNK];
+        du += q[3 * CHUNK];
         vs = fmaxf(vs, (float)q[4 * CHUNK]);
-        Ss += (float)q[5 * CHUNK];
+        Ss += q[5 * CHUNK];
         nn += (int)q[6 * CHUNK];
         hs += (uint64_t)__double_as_longlong(q[7 * CHUNK]);
     }
     a.ax[p] = (float)tx;
     a.ay[p] = (float)ty;
     a.az[p] = (float)tz;
-    a.du[p] = du;
+    a.du[p] = (float)du;
     a.vsig[p] = vs;
-    a.S[p] = Ss;
+    a.S[p] = (float)Ss;
     a.nf[p] = nn;
     if (HASH) a.hash[p] = hs;
 }

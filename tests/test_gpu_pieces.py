@@ -160,3 +160,28 @@ def test_pieces_bounded_per_particle(sph, ctx):
         assert np.array_equal(a[0][k], u[0][k]), k
     for k in a[1]:
         assert np.array_equal(a[1][k], u[1][k]), k
+
+
+def test_split_sums_of_many_neighbours(sph, ctx):
+    """S of chunks split into 16 pieces, 2000 partners a particle: the pieces'
+    FP64 sums are rounded once, at the end.  The unsplit sums have the same
+    terms in other tiles of 64, so that the two differ by the tiles' FP32
+    roundings and two final ones: 0.27 to 0.42 units in the last place (root
+    mean square, simulated with random terms, 30% to 90% of a tile in range);
+    pieces added in FP32 would make it 0.68 to 0.72."""
+    n = 16000
+    ps = sphinputs.uniform(n, 95, velocity=True)
+    h = np.full(n, np.float32((3.0 * 2000 / (4.0 * np.pi * n)) ** (1.0 / 3.0)) * ps.box, dtype=np.float64)
+    h = I.f32(h)
+    (a,), ta = run_fixed(sph, ctx, [ps], [h], piece_records=4096)
+    (u,), tu = run_fixed(sph, ctx, [ps], [h], piece_records=-1)
+    st = ta.stats()
+    assert st["pieces"] == 16 * st["heavy_chunks"] and st["heavy_chunks"] == st["chunks"], st
+    assert tu.stats()["pieces"] == 0
+    for k in ("nforce", "hash", "vsig"):
+        assert np.array_equal(a[1][k], u[1][k]), k
+    assert a[1]["nforce"].mean() > 1500
+    d = (a[1]["S"].astype(np.float64) - u[1]["S"]) / np.spacing(u[1]["S"])
+    rms = float(np.sqrt(np.mean(d * d)))
+    print(f"rms difference {rms:.3f} units in the last place, largest {np.abs(d).max():.0f}")
+    assert rms <= 0.55
