@@ -22,8 +22,8 @@
  *    (sph_tree_workspace_needed says how much to offer, then build again).
  *    Without a workspace the library allocates the tree's buffers itself
  *    (hipMalloc, grow-only; a growth frees the old buffer, which waits for
- *    the device) and frees them in sph_tree_destroy.  A context allocates a
- *    4 KiB device counter block and 64 KiB of pinned host memory once.
+ *    the device) and frees them in sph_tree_destroy.  A context allocates an
+ *    8 KiB device counter block and 64.5 KiB of pinned host memory once.
  *  - One context per HIP stream.  Every call enqueues work on the context's
  *    stream; outputs are valid once that stream has been synchronised, except
  *    where a host output is documented (those calls synchronise).
@@ -377,6 +377,12 @@ sph_status sph_last_work(sph_ctx* ctx, uint64_t* density_pairs, uint64_t* force_
  * context's stream.  Errors: SPH_E_ARG, SPH_E_HIP. */
 sph_status sph_last_reads(sph_ctx* ctx, uint64_t* density_records, uint64_t* force_records);
 
+/* Walks that waves parked near the end of a pass and blocks went on with, in
+ * the same passes as sph_last_work counts (which walks are parked depends on
+ * the passes' timing, the results do not): *density_walks and *force_walks
+ * [host].  Synchronises the context's stream.  Errors: SPH_E_ARG, SPH_E_HIP. */
+sph_status sph_last_parked(sph_ctx* ctx, uint64_t* density_walks, uint64_t* force_walks);
+
 /* Enable (1) or disable (0) per-stage event timing on the context. */
 void sph_enable_timing(sph_ctx* ctx, int32_t on);
 
@@ -385,7 +391,9 @@ void sph_enable_timing(sph_ctx* ctx, int32_t on);
  * [7] levels, [8] top cells per side of set 0, [9] max leaf size, [10] HIP
  * graphs captured and instantiated by sph_run_graph on this tree so far,
  * [11] heavy chunks (handed out first, see sph_params.piece_records), [12]
- * their pieces.
+ * their pieces, [13] slots for parked walks, [14] the stages whose chunks
+ * blocks walk from their start (1 density, 2 force, 3 both; both numbers as of
+ * the last density, solve, force or graph call).
  * May synchronise the tree's stream (a count the sort kept on the device). */
 sph_status sph_tree_stats(const sph_tree* t, int64_t* stats, int32_t cap);
 

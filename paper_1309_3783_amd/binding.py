@@ -28,7 +28,8 @@ EXPORTS = ["sph_version", "sph_status_str", "sph_params_default", "sph_ctx_creat
            "sph_tree_destroy", "sph_tree_bytes", "sph_tree_set_workspace", "sph_tree_workspace_needed",
            "sph_build_cells", "sph_build_cells_static", "sph_refresh_cells", "sph_sort_pairs", "sph_density",
            "sph_solve_h", "sph_force", "sph_set_halo", "sph_run_graph", "sph_last_timings", "sph_last_work",
-           "sph_last_reads", "sph_enable_timing", "sph_tree_stats", "sph_kick", "sph_drift", "sph_cfl_dt"]
+           "sph_last_reads", "sph_last_parked", "sph_enable_timing", "sph_tree_stats", "sph_kick", "sph_drift",
+           "sph_cfl_dt"]
 
 
 class sph_params(C.Structure):
@@ -109,6 +110,7 @@ def lib():
         L.sph_last_timings.restype = C.c_int32
         L.sph_last_work.argtypes = [vp, C.POINTER(C.c_uint64), C.POINTER(C.c_uint64)]
         L.sph_last_reads.argtypes = [vp, C.POINTER(C.c_uint64), C.POINTER(C.c_uint64)]
+        L.sph_last_parked.argtypes = [vp, C.POINTER(C.c_uint64), C.POINTER(C.c_uint64)]
         L.sph_enable_timing.argtypes = [vp, C.c_int32]
         L.sph_enable_timing.restype = None
         L.sph_tree_stats.argtypes = [vp, C.POINTER(C.c_int64), C.c_int32]
@@ -119,7 +121,7 @@ def lib():
                      "sph_tree_bytes", "sph_tree_set_workspace", "sph_tree_workspace_needed", "sph_build_cells",
                      "sph_build_cells_static", "sph_refresh_cells", "sph_sort_pairs", "sph_density", "sph_solve_h",
                      "sph_force", "sph_run_graph", "sph_tree_stats", "sph_kick", "sph_drift", "sph_cfl_dt",
-                     "sph_last_work", "sph_last_reads", "sph_set_halo"):
+                     "sph_last_work", "sph_last_reads", "sph_last_parked", "sph_set_halo"):
             getattr(L, name).restype = st
         _lib = L
     return _lib
@@ -202,6 +204,13 @@ class Context:
         """(density records loaded, force records loaded) of the same calls."""
         d, f = C.c_uint64(0), C.c_uint64(0)
         self.check(lib().sph_last_reads(self.h, C.byref(d), C.byref(f)), "sph_last_reads")
+        return int(d.value), int(f.value)
+
+    def parked(self):
+        """(density walks, force walks) that waves parked and blocks went on
+        with, in the same calls."""
+        d, f = C.c_uint64(0), C.c_uint64(0)
+        self.check(lib().sph_last_parked(self.h, C.byref(d), C.byref(f)), "sph_last_parked")
         return int(d.value), int(f.value)
 
     def close(self):
@@ -462,10 +471,10 @@ class Tree:
                                                C.byref(self._gf), _ptr(unconv)), "sph_run_graph")
 
     def stats(self) -> dict:
-        v = (C.c_int64 * 13)()
-        self.ctx.check(lib().sph_tree_stats(self.h, v, 13), "sph_tree_stats")
+        v = (C.c_int64 * 15)()
+        self.ctx.check(lib().sph_tree_stats(self.h, v, 15), "sph_tree_stats")
         keys = ["particles", "cells", "leaves", "tasks", "pair_tasks", "sorted_entries", "chunks", "levels",
-                "top_grid", "max_leaf", "graph_captures", "heavy_chunks", "pieces"]
+                "top_grid", "max_leaf", "graph_captures", "heavy_chunks", "pieces", "park_slots", "block_walks"]
         return dict(zip(keys, [int(x) for x in v]))
 
     def bytes(self) -> int:

@@ -316,9 +316,10 @@ int32_t sph_last_timings(sph_ctx* ctx, const char** names, double* ms, int32_t c
     return k;
 }
 
-sph_status sph_last_work(sph_ctx* ctx, uint64_t* density_pairs, uint64_t* force_pairs) {
+// The word-th of each of a stage's 8 counters (64 bits, 128 bytes apart), added
+// up: density, then force.
+static sph_status read_work(sph_ctx* ctx, int word, uint64_t* density, uint64_t* force) {
     if (!ctx) return SPH_E_ARG;
-    // 2 x 8 counters of 64 bits, 128 bytes apart
     const void* d = ctx->d_counter + sph_ctx::CTR_WORK;
     if (hipMemcpyAsync(ctx->h_pin, d, 512 * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
         hipStreamSynchronize(ctx->stream) != hipSuccess)
@@ -326,26 +327,22 @@ sph_status sph_last_work(sph_ctx* ctx, uint64_t* density_pairs, uint64_t* force_
     const uint64_t* v = (const uint64_t*)ctx->h_pin;
     uint64_t s[2] = {0, 0};
     for (int k = 0; k < 2; ++k)
-        for (int g = 0; g < 8; ++g) s[k] += v[k * 128 + g * 16];
-    if (density_pairs) *density_pairs = s[0];
-    if (force_pairs) *force_pairs = s[1];
+        for (int g = 0; g < 8; ++g) s[k] += v[k * 128 + g * 16 + word];
+    if (density) *density = s[0];
+    if (force) *force = s[1];
     return SPH_OK;
 }
 
+sph_status sph_last_work(sph_ctx* ctx, uint64_t* density_pairs, uint64_t* force_pairs) {
+    return read_work(ctx, 0, density_pairs, force_pairs);
+}
+
 sph_status sph_last_reads(sph_ctx* ctx, uint64_t* density_records, uint64_t* force_records) {
-    if (!ctx) return SPH_E_ARG;
-    // the word after each pair-evaluation counter
-    const void* d = ctx->d_counter + sph_ctx::CTR_WORK;
-    if (hipMemcpyAsync(ctx->h_pin, d, 512 * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
-        hipStreamSynchronize(ctx->stream) != hipSuccess)
-        return SPH_E_HIP;
-    const uint64_t* v = (const uint64_t*)ctx->h_pin;
-    uint64_t s[2] = {0, 0};
-    for (int k = 0; k < 2; ++k)
-        for (int g = 0; g < 8; ++g) s[k] += v[k * 128 + g * 16 + 1];
-    if (density_records) *density_records = s[0];
-    if (force_records) *force_records = s[1];
-    return SPH_OK;
+    return read_work(ctx, 1, density_records, force_records);
+}
+
+sph_status sph_last_parked(sph_ctx* ctx, uint64_t* density_walks, uint64_t* force_walks) {
+    return read_work(ctx, 2, density_walks, force_walks);
 }
 
 void sph_enable_timing(sph_ctx* ctx, int32_t on) {
@@ -363,7 +360,7 @@ sph_status sph_tree_stats(const sph_tree* t, int64_t* stats, int32_t cap) {
             return SPH_E_HIP;
         const_cast<sph_tree*>(t)->nsegent = v;
     }
-    int64_t v[13] = {t->n,
+    int64_t v[15] = {t->n,
                      t->ncells,
                      t->nleaves,
                      t->ntasks,
@@ -375,8 +372,10 @@ sph_status sph_tree_stats(const sph_tree* t, int64_t* stats, int32_t cap) {
                      t->max_leaf,
                      t->graph_captures,
                      t->nheavy,
-                     t->npieces};
-    for (int i = 0; i < cap && i < 13; ++i) stats[i] = v[i];
+                     t->npieces,
+                     t->nslots,
+                     (t->direct_density ? 1 : 0) | (t->direct ? 2 : 0)};
+    for (int i = 0; i < cap && i < 15; ++i) stats[i] = v[i];
     return SPH_OK;
 }
 

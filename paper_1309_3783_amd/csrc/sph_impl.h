@@ -29,9 +29,10 @@ struct sph_ctx {
     std::vector<std::pair<const char*, double>> last_ms;
     // device words (CTR_WORDS): [0, 256) density work counters, [256, 512)
     // force work counters, [512, 768) chunk-list counts, [CTR_CFL] Courant
-    // minimum, [CTR_WORK, +512): 64-bit counts of pair evaluations, density
-    // then force, each spread over 8 counters 128 bytes apart, [CTR_PARK] and
-    // 128 bytes on: walks parked in a density / force pass
+    // minimum, [CTR_WORK, +512): 64-bit counts of pair evaluations, records
+    // loaded and parked walks taken up, density then force, each spread over 8
+    // counters 128 bytes apart, [CTR_PARK] and 128 bytes on: slots asked for
+    // in a density / force pass
     int32_t* d_counter = nullptr;
     static constexpr int CTR_CFL = 768;
     static constexpr int CTR_WORK = 1024;
@@ -47,6 +48,9 @@ struct sph_ctx {
     static constexpr size_t PIN_SOLVE = PIN_BYTES;
     static constexpr size_t PIN_DONE = PIN_BYTES + 256;
     static constexpr size_t PIN_ALL = PIN_BYTES + 512;
+    static_assert(PIN_SOLVE >= PIN_BYTES && PIN_DONE >= PIN_SOLVE + 8 * sizeof(int32_t) &&
+                      PIN_ALL >= PIN_DONE + sizeof(uint32_t),
+                  "the words that the host polls lie apart from a read-back and from each other");
     void* h_pin = nullptr;
     uint32_t pin_seq = 0;
     uint32_t next_seq() { return ++pin_seq ? pin_seq : ++pin_seq; }

@@ -368,7 +368,8 @@ __device__ __forceinline__ int wave_count(int v) {
 }
 // ... and added up once per wave when it leaves the kernel, into one of 8
 // counters 128 bytes apart (one same-address atomic per wave step from the
-// whole GPU would serialise); the records loaded go to the word after each.
+// whole GPU would serialise); the records loaded go to the word after each,
+// the parked walks that blocks went on with to the next.
 __device__ __forceinline__ void flush_work(unsigned long long* work, unsigned long long v) {
     if ((threadIdx.x & 63) == 0 && v) atomicAdd(work + 16 * (blockIdx.x & 7), v);
 }
@@ -1251,6 +1252,7 @@ __device__ __forceinline__ void run_teams(const typename P::Args& a, PassLds<P, 
         M.cnt[w][0] = 0ull;
         M.cnt[w][1] = 0ull;
     }
+    int parked = 0;   // walks taken up
     for (int it = blockIdx.x; it < items; it += gridDim.x) {
         int leaf, p0, cnt;
         uint64_t pend, amask = 0;
@@ -1258,6 +1260,7 @@ __device__ __forceinline__ void run_teams(const typename P::Args& a, PassLds<P, 
         Cursor cur{};
         typename P::Acc acc;
         if (!DIRECT) {
+            ++parked;
             const char* slot = a.park + (size_t)it * PARK_BYTES;
             const Parked& k = *(const Parked*)slot;
             leaf = uni(k.leaf);
@@ -1305,6 +1308,7 @@ __device__ __forceinline__ void run_teams(const typename P::Args& a, PassLds<P, 
     if (lane == 0) {
         flush_work(a.work, M.cnt[w][0]);
         flush_work(a.work + 1, M.cnt[w][1]);
+        if (!DIRECT && w == 0) flush_work(a.work + 2, (unsigned long long)parked);
     }
 }
 

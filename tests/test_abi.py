@@ -123,3 +123,7 @@ def test_counters_reject_a_null_context():
     L = sph.lib()
     assert L.sph_last_work(None, None, None) == binding.SPH_E_ARG
     assert L.sph_last_reads(None, None, None) == binding.SPH_E_ARG
+
+
+def test_parked_walks_reject_a_null_context():
+    assert sph.lib().sph_last_parked(None, None, None) == binding.SPH_E_ARG
