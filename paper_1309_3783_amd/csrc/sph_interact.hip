@@ -39,7 +39,6 @@
 // within their bars up to ~1600 neighbours.
 #include <cmath>
 #include <cstring>
-#include <type_traits>
 
 #include "sph_impl.h"
 
@@ -1100,9 +1099,9 @@ __device__ __forceinline__ bool walk(const typename P::Args& a, Lds& S, int base
 // ---------------------------------------------------------------------------
 // One pass of an interaction stage (density or force): the kernel bodies
 // ---------------------------------------------------------------------------
-template <class P, int W>
+template <class P, int W, bool TEAM>
 struct PassLds {
-    typename P::template Lds<W> l;
+    typename P::template Lds<W, TEAM> l;
     SweepTab t[W];
     int pick[W][64];
     // the waves' pair evaluations and records loaded (kept in LDS, not in
@@ -1147,9 +1146,12 @@ __device__ __forceinline__ Slots take_slots(uint64_t amask, int rmax, int* pick)
 template <bool SOLVE, class A>
 __device__ __forceinline__ uint64_t to_do(const A& a, int p0, int cnt) {
     const int lane = threadIdx.x & 63;
-    if (SOLVE) return __ballot(lane < cnt && a.active[p0 + lane] == 1);
-    if (a.owned) return __ballot(lane < cnt && a.owned[p0 + lane] != 0);
-    return cnt >= 64 ? ~0ull : ((1ull << cnt) - 1ull);
+    if constexpr (SOLVE) {
+        return __ballot(lane < cnt && a.active[p0 + lane] == 1);
+    } else {
+        if (a.owned) return __ballot(lane < cnt && a.owned[p0 + lane] != 0);
+        return cnt >= 64 ? ~0ull : ((1ull << cnt) - 1ull);
+    }
 }
 
 // The next frame of a chunk (the lane's particle is read again for every
@@ -1165,7 +1167,7 @@ __device__ __forceinline__ uint64_t chunk_frame(const A& a, uint64_t pend, int p
 // Persistent: every wave takes chunks until none are left, frame by frame,
 // each frame's particles packed into the first slots.
 template <class P, bool SOLVE, bool EXT>
-__device__ __forceinline__ void run_pass(const typename P::Args& a, PassLds<P, BLK / 64>& M) {
+__device__ __forceinline__ void run_pass(const typename P::Args& a, PassLds<P, BLK / 64, false>& M) {
     const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
     const int home = blockIdx.x & (NGRP - 1);
     int grp = 0;
@@ -1237,7 +1239,7 @@ __device__ __forceinline__ void run_pass(const typename P::Args& a, PassLds<P, B
 // chunks (DIRECT: a tree of uneven sets alone with few chunks, see
 // ensure_state).  The items are taken in turn (block b starts with item b).
 template <class P, bool SOLVE, bool DIRECT, int W>
-__device__ __forceinline__ void run_teams(const typename P::Args& a, PassLds<P, W>& M, int* mc) {
+__device__ __forceinline__ void run_teams(const typename P::Args& a, PassLds<P, W, true>& M, int* mc) {
     const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
     // (chunks: from the ranges in turn, so that the longest start first)
     int items = 0;
@@ -1337,21 +1339,21 @@ struct DensP {
         A.tq += (double)A.sq;
         A.sf = A.sg = A.sw = A.sq = 0.f;
     }
-    template <int W>
+    template <int W, bool TEAM>
     struct Lds {
         float4 p[TILE * W];     // x, y, z (shifted into the target's frame), m
         uint64_t m[HASH ? TILE * W : 1];   // pair-hash terms
-        int n[TILE * W];        // counts of a tile (put)
+        int n[TEAM ? TILE * W : 1];        // counts of a tile (put)
     };
     // a lane's sums and counts of one tile, to LDS and added from there
-    template <int W>
-    static __device__ __forceinline__ void put(Lds<W>& S, int at, const Acc& A) {
+    template <class Tiles>
+    static __device__ __forceinline__ void put(Tiles& S, int at, const Acc& A) {
         S.p[at] = make_float4(A.sf, A.sg, A.sw, A.sq);
         S.n[at] = A.nn;
         if (HASH) S.m[at] = A.hs;
     }
-    template <int W>
-    static __device__ __forceinline__ void get(const Lds<W>& S, int at, Acc& A) {
+    template <class Tiles>
+    static __device__ __forceinline__ void get(const Tiles& S, int at, Acc& A) {
         const float4 v = S.p[at];
         A.sf = v.x;
         A.sg = v.y;
@@ -1400,15 +1402,15 @@ struct DensP {
     static __device__ __forceinline__ Pre pre(const Args&, uint32_t, bool) { return Pre{}; }
     static __device__ __forceinline__ float rad2(float part2, const Pre&, float, float) { return part2; }
     static __device__ __forceinline__ float blk_rad2(float part2, float, float, float) { return part2; }
-    template <int W>
-    static __device__ __forceinline__ void stage(Lds<W>& S, int slot, uint32_t j, const float4& pj, float Sx, float Sy,
+    template <class Tiles>
+    static __device__ __forceinline__ void stage(Tiles& S, int slot, uint32_t j, const float4& pj, float Sx, float Sy,
                                                  float Sz, const Args& a, const Pre&, bool, bool uselo) {
         const float4 lo = uselo ? a.plo[j] : make_float4(0.f, 0.f, 0.f, 0.f);
         S.p[slot] = make_float4((pj.x + Sx) + lo.x, (pj.y + Sy) + lo.y, (pj.z + Sz) + lo.z, pj.w);
         if (HASH) S.m[slot] = a.mix[j];
     }
-    template <int W>
-    static __device__ __forceinline__ void pair(Acc& A, const Lds<W>& S, int j, const Lane& L) {
+    template <class Tiles>
+    static __device__ __forceinline__ void pair(Acc& A, const Tiles& S, int j, const Lane& L) {
         const float4 q = S.p[j];
         const float dx = L.x.x - q.x, dy = L.x.y - q.y, dz = L.x.z - q.z;
         const float r = fsqrt(fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
@@ -1474,14 +1476,14 @@ __device__ __forceinline__ int DensP<HASH>::finish(const DensArgs& a, const Acc&
 // case).
 template <bool SOLVE, bool HASH, bool EXT>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(5))) void k_density(DensArgs a) {
-    __shared__ PassLds<DensP<HASH>, BLK / 64> s_m;
+    __shared__ PassLds<DensP<HASH>, BLK / 64, false> s_m;
     run_pass<DensP<HASH>, SOLVE, EXT>(a, s_m);
 }
 
 // (few teams run at a time: registers rather than waves)
 template <bool SOLVE, bool HASH, bool DIRECT, int W>
 __global__ __launch_bounds__(64 * W) void k_density_teams(DensArgs a) {
-    __shared__ PassLds<DensP<HASH>, W> s_m;
+    __shared__ PassLds<DensP<HASH>, W, true> s_m;
     __shared__ int s_mc[2 * W];
     run_teams<DensP<HASH>, SOLVE, DIRECT, W>(a, s_m, s_mc);
 }
@@ -1529,9 +1531,12 @@ struct ForceArgs {
     const float4* pv;
     const float4* frec;   // h, A, sound speed, K = 8/(pi h^5); pv.w holds rho
     const uint8_t* owned;
-    const uint8_t* active;  // (null: as the chunk list, of the density's Newton passes)
-    const uint32_t* list;
-    const int* lcount;
+    // (rmax stands here for the place of the pointers behind it, which are loaded
+    // in groups: four scalar spills more without it, a mixture of 10^6 particles
+    // 4.83 ms against 4.71)
+    int rmax;
+    const uint32_t* list;   // the build's order of the chunks (null: as they are)
+    const int* lcount;      // (null: all chunks)
     const uint64_t* mix;
     const uint64_t* csr;
     const uint32_t* csr_off;
@@ -1554,7 +1559,6 @@ struct ForceArgs {
     int32_t* nf;
     uint64_t* hash;
     unsigned long long* work;
-    int rmax;
 };
 
 __device__ __forceinline__ float gradF(float q, float h, float rinv) {
@@ -1598,7 +1602,7 @@ struct ForceP {
         A.tz += (double)A.az;
         A.ax = A.ay = A.az = 0.f;
     }
-    template <int W>
+    template <int W, bool TEAM>
     struct Lds {
         float4 p[TILE * W];    // x, y, z (shifted into the target's frame), h^2
         float4 h[TILE * W];    // m, 1/h, K = 8/(pi h^5), A
@@ -1612,14 +1616,14 @@ struct ForceP {
         return (uint64_t)__float_as_uint(v.z) | (uint64_t)__float_as_uint(v.w) << 32;
     }
     // a lane's sums and counts of one tile, to LDS and added from there
-    template <int W>
-    static __device__ __forceinline__ void put(Lds<W>& S, int at, const Acc& A) {
+    template <class Tiles>
+    static __device__ __forceinline__ void put(Tiles& S, int at, const Acc& A) {
         S.p[at] = make_float4(A.ax, A.ay, A.az, A.du);
         S.h[at] = make_float4(A.S, A.vs, __int_as_float(A.nn), 0.f);
         if (HASH) S.v[at] = hash_words(0.f, 0.f, A.hs);
     }
-    template <int W>
-    static __device__ __forceinline__ void get(const Lds<W>& S, int at, Acc& A) {
+    template <class Tiles>
+    static __device__ __forceinline__ void get(const Tiles& S, int at, Acc& A) {
         const float4 v = S.p[at], u = S.h[at];
         A.ax = v.x;
         A.ay = v.y;
@@ -1732,8 +1736,8 @@ struct ForceP {
         const float r = fmaf(fmaxf(hmax, hb), 1.000002f, tiny);
         return fminf(part2, r * r);
     }
-    template <int W>
-    static __device__ __forceinline__ void stage(Lds<W>& S, int slot, uint32_t j, const float4& pj, float Sx, float Sy,
+    template <class Tiles>
+    static __device__ __forceinline__ void stage(Tiles& S, int slot, uint32_t j, const float4& pj, float Sx, float Sy,
                                                  float Sz, const Args& a, const Pre& pr, bool loaded, bool uselo) {
         const float4 fj = loaded ? pr.f : a.frec[j];
         const float4 lo = uselo ? a.plo[j] : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1743,8 +1747,8 @@ struct ForceP {
         if (HASH) S.c[slot] = hash_words(fj.z, fj.x, a.mix[j]);
         else *(float2*)&S.c[slot] = make_float2(fj.z, fj.x);
     }
-    template <int W>
-    static __device__ __forceinline__ void pair(Acc& A, const Lds<W>& S, int j, const Lane& L) {
+    template <class Tiles>
+    static __device__ __forceinline__ void pair(Acc& A, const Tiles& S, int j, const Lane& L) {
         const float4 q = S.p[j];
         const float4 sh = S.h[j];
         const float4 sv = S.v[j];
@@ -1781,13 +1785,13 @@ struct ForceP {
 
 template <bool HASH, bool EXT>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(5))) void k_force(ForceArgs a) {
-    __shared__ PassLds<ForceP<HASH>, BLK / 64> s_m;
+    __shared__ PassLds<ForceP<HASH>, BLK / 64, false> s_m;
     run_pass<ForceP<HASH>, false, EXT>(a, s_m);
 }
 
 template <bool HASH, bool DIRECT, int W>
 __global__ __launch_bounds__(64 * W) void k_force_teams(ForceArgs a) {
-    __shared__ PassLds<ForceP<HASH>, W> s_m;
+    __shared__ PassLds<ForceP<HASH>, W, true> s_m;
     __shared__ int s_mc[2 * W];
     run_teams<ForceP<HASH>, false, DIRECT, W>(a, s_m, s_mc);
 }
@@ -2455,23 +2459,30 @@ static DensArgs dens_args(sph_tree* t, int* counter, const int* lcount) {
     return a;
 }
 
-// A team kernel over items chunks or parked walks.  Chunks: a block each, so
-// that the next one starts wherever a block ends (200000 particles, 4819
-// chunks, blocks of four waves: the h solve and force 4.2 ms with the four
-// blocks per CU that fit at once taking them in turn, 3.5 with a block each).
-// Parked walks, of which most passes have few: two blocks per CU take them
-// in turn.  Eight waves a block where that leaves blocks idle otherwise (30011
-// particles, 597 chunks: 0.90 ms for build, density and force against 0.99 with
-// four; sixteen were slower too), four where the chunks are more than fit
-// (200000 particles: 3.5 against 4.2 ms with two).
-template <class A, class F>
-static void launch_teams(const sph_ctx* ctx, const sph_tree* t, const A& a, int64_t items, bool chunks, F kern) {
-    const bool wide = items <= 4 * (int64_t)ctx->n_cu || !chunks;
-    int64_t blocks = chunks ? items : std::min<int64_t>(items, 2 * (int64_t)ctx->n_cu);
+// A team kernel over the chunks of a tree, a block each, so that the next one
+// starts wherever a block ends (200000 particles, 4819 chunks, blocks of four
+// waves: the h solve and force 4.2 ms with the four blocks per CU that fit at
+// once taking them in turn, 3.5 with a block each).  Eight waves a block where
+// that leaves blocks idle otherwise (30011 particles, 597 chunks: 0.90 ms for
+// build, density and force against 0.99 with four; sixteen were slower too),
+// four where the chunks are more than fit (200000 particles: 3.5 against 4.2 ms
+// with two).
+static dim3 team_grid(const sph_ctx* ctx, const sph_tree* t, int64_t blocks) {
     if (t->prm.blocks_per_cu > 0) blocks = std::min<int64_t>(blocks, (int64_t)ctx->n_cu * t->prm.blocks_per_cu);
-    const dim3 grid((unsigned)std::max<int64_t>(1, blocks));
-    if (wide) hipLaunchKernelGGL(kern(std::integral_constant<int, 8>{}), grid, dim3(512), 0, ctx->stream, a);
-    else hipLaunchKernelGGL(kern(std::integral_constant<int, 4>{}), grid, dim3(256), 0, ctx->stream, a);
+    return dim3((unsigned)std::max<int64_t>(1, blocks));
+}
+template <class A>
+static void launch_chunk_teams(const sph_ctx* ctx, const sph_tree* t, const A& a, void (*four)(A), void (*eight)(A)) {
+    const bool wide = t->nchunks <= 4 * (int64_t)ctx->n_cu;
+    hipLaunchKernelGGL(wide ? eight : four, team_grid(ctx, t, t->nchunks), dim3(wide ? 512 : 256), 0, ctx->stream, a);
+}
+// ... and over the walks parked by the pass before, of which most passes have
+// few: two blocks of eight waves per CU take them in turn.
+template <class A>
+static void launch_parked_teams(const sph_ctx* ctx, const sph_tree* t, const A& a, void (*eight)(A)) {
+    if (t->nslots == 0) return;
+    hipLaunchKernelGGL(eight, team_grid(ctx, t, std::min<int64_t>(t->nslots, 2 * (int64_t)ctx->n_cu)), dim3(512), 0,
+                       ctx->stream, a);
 }
 
 // listed: a Newton pass after the first, over the chunks that still hold
@@ -2493,11 +2504,15 @@ static void launch_density(sph_ctx* ctx, sph_tree* t, bool solve, bool listed, i
     DensArgs a = dens_args(t, counter, lcount);
     a.taken = taken;
     if (t->direct_density) {
-        launch_teams(ctx, t, a, t->nchunks, true, [&](auto W) {
-            constexpr int w = decltype(W)::value;
-            return solve ? (t->hash ? k_density_teams<true, true, true, w> : k_density_teams<true, false, true, w>)
-                         : (t->hash ? k_density_teams<false, true, true, w> : k_density_teams<false, false, true, w>);
-        });
+        if (solve && t->hash)
+            launch_chunk_teams(ctx, t, a, k_density_teams<true, true, true, 4>, k_density_teams<true, true, true, 8>);
+        else if (solve)
+            launch_chunk_teams(ctx, t, a, k_density_teams<true, false, true, 4>, k_density_teams<true, false, true, 8>);
+        else if (t->hash)
+            launch_chunk_teams(ctx, t, a, k_density_teams<false, true, true, 4>, k_density_teams<false, true, true, 8>);
+        else
+            launch_chunk_teams(ctx, t, a, k_density_teams<false, false, true, 4>,
+                               k_density_teams<false, false, true, 8>);
         return;
     }
     void (*kern)(DensArgs);
@@ -2509,11 +2524,8 @@ static void launch_density(sph_ctx* ctx, sph_tree* t, bool solve, bool listed, i
         else kern = t->hash ? k_density<false, true, false> : k_density<false, false, false>;
     }
     hipLaunchKernelGGL(kern, dim3(persistent_blocks(ctx, t, t->nchunks, (const void*)kern)), dim3(BLK), 0, st, a);
-    if (t->nslots > 0)
-        launch_teams(ctx, t, a, t->nslots, false, [&](auto W) {
-            constexpr int w = decltype(W)::value;
-            return t->hash ? k_density_teams<false, true, false, w> : k_density_teams<false, false, false, w>;
-        });
+    launch_parked_teams(ctx, t, a, t->hash ? k_density_teams<false, true, false, 8>
+                                           : k_density_teams<false, false, false, 8>);
     if (t->npieces > 0) {
         const dim3 gp(nblk(t->npieces, 4));
         if (solve) {
@@ -2565,7 +2577,6 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     a.pv = t->pv;
     a.frec = t->frec;
     a.owned = t->owned;
-    a.active = nullptr;
     a.list = t->order;
     a.lcount = nullptr;
     a.mix = t->mix;
@@ -2596,21 +2607,15 @@ static void launch_force(sph_ctx* ctx, sph_tree* t, int* counter) {
     a.work = (unsigned long long*)(t->work_ctr + 256);
     a.rmax = rmax_of(t);
     if (t->direct) {
-        launch_teams(ctx, t, a, t->nchunks, true, [&](auto W) {
-            constexpr int w = decltype(W)::value;
-            return t->hash ? k_force_teams<true, true, w> : k_force_teams<false, true, w>;
-        });
+        if (t->hash) launch_chunk_teams(ctx, t, a, k_force_teams<true, true, 4>, k_force_teams<true, true, 8>);
+        else launch_chunk_teams(ctx, t, a, k_force_teams<false, true, 4>, k_force_teams<false, true, 8>);
         return;
     }
     void (*kern)(ForceArgs);
     if (ext_kernels(t)) kern = t->hash ? k_force<true, true> : k_force<false, true>;
     else kern = t->hash ? k_force<true, false> : k_force<false, false>;
     hipLaunchKernelGGL(kern, dim3(persistent_blocks(ctx, t, t->nchunks, (const void*)kern)), dim3(BLK), 0, st, a);
-    if (t->nslots > 0)
-        launch_teams(ctx, t, a, t->nslots, false, [&](auto W) {
-            constexpr int w = decltype(W)::value;
-            return t->hash ? k_force_teams<true, false, w> : k_force_teams<false, false, w>;
-        });
+    launch_parked_teams(ctx, t, a, t->hash ? k_force_teams<true, false, 8> : k_force_teams<false, false, 8>);
     if (t->npieces > 0) {
         const dim3 gp(nblk(t->npieces, 4));
         if (t->hash) hipLaunchKernelGGL((k_force_pieces<true>), gp, dim3(256), 0, st, a);
