@@ -1326,7 +1326,7 @@ __device__ __forceinline__ void block_list(const Cell& C, int ax, int n, float l
 
 // Segments of 65..SEG_LDS_MAX entries (their (cell, axis) indices listed in
 // sel): those of at most WAVE_SORT_MAX entries sorted by one wave each
-// (69 registers: sixteen keys per lane would leave room for half the waves),
+// (63 registers: sixteen keys per lane would leave room for half the waves),
 // the longer ones by a block each, in two kernels.
 constexpr int WAVE_SORT_MAX = 512;
 static_assert(SEG_LDS_MAX == 256 * 16, "the block's threads hold the whole list");

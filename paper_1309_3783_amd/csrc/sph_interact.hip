@@ -33,10 +33,14 @@
 // acceleration are summed in FP32 within one staged tile (at most 64 terms
 // per lane) and accumulated across tiles in FP64 (blocked compensated
 // summation), so their rounding stays below ~65 units in the last place of
-// the sum of magnitudes for any number of neighbours.  du/dt and the error
-// scale S are plain FP32 sums (registers: carrying them in FP64 too would
-// cost the force kernel a wave per SIMD); the recursive-sum bound keeps them
-// within their bars up to ~1600 neighbours.
+// the sum of magnitudes for any number of neighbours.  So are du/dt and the
+// error scale S in uneven sets (some cell bisected, or a top cell of SCAN_MIN
+// particles: SetInfo::uneven), split chunks included.  In the other sets they
+// run on in FP32 over a chunk's tiles; the recursive-sum bound keeps them
+// within their bars up to ~1600 neighbours.  (Per tile there too they would
+// take the one-level force kernel 92 vector registers instead of 90, of the 96
+// that five waves per SIMD allow, and no time: the h solve and force of a
+// lattice of 10^6 1499 us either way.  Their last bits would be others.)
 #include <cmath>
 #include <cstring>
 
@@ -1236,8 +1240,8 @@ __device__ __forceinline__ void run_pass(const typename P::Args& a, PassLds<P, B
 }
 
 // Blocks as teams: the walks parked by run_pass (DIRECT false), or whole
-// chunks (DIRECT: a tree of uneven sets alone with few chunks, see
-// ensure_state).  The items are taken in turn (block b starts with item b).
+// chunks (DIRECT: a tree of uneven sets alone with few chunks and no pieces,
+// see ensure_state).  The items are taken in turn (block b starts with item b).
 template <class P, bool SOLVE, bool DIRECT, int W>
 __device__ __forceinline__ void run_teams(const typename P::Args& a, PassLds<P, W, true>& M, int* mc) {
     const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
@@ -2344,10 +2348,16 @@ static Err ensure_state(const sph_ctx* ctx, sph_tree* t) {
     t->fS = t->fvs + n;
     t->fn = (int32_t*)(t->fS + n);
     // who walks the chunks (see walk): blocks from the start where every set is
-    // uneven and there are no more chunks than waves fit (200000 particles, 4819
-    // chunks: the h solve and force 5.0 ms by blocks, 5.8 by waves that park their
-    // long walks); else waves, with slots for the walks they park, where the
-    // tree has long walks at all.  More than PARK_SLOTS walks (eight per CU)
+    // uneven (nplain: a set that is not has du and S that one wave adds up; the
+    // density goes with them), no chunk is split (a piece is a wave's) and there
+    // are at most as many chunks as waves fit; else waves, with slots for the
+    // walks they park, where the tree has long walks at all.  Build, h solve and
+    // force of one mixture by blocks / by waves that park, without pieces: 30011
+    // particles (564 chunks) 1.39 / 2.93 ms, 200000 (4809) 3.1 / 4.9, beyond the
+    // line 260003 (5933) 3.8 / 5.6, 500009 (10346) 6.5 / 7.2, 10^6 (20279) 11.3 /
+    // 9.9 (with its pieces 9.35).  So the line lies at the waves that fit, not
+    // where the two cross; most trees of more chunks have pieces, with which
+    // blocks do not walk at all.  More than PARK_SLOTS walks (eight per CU)
     // parked at a time would be no tail.
     t->direct = t->ext() && t->nplain == 0 && t->npieces == 0 && t->nchunks <= 20 * (int64_t)ctx->n_cu;
     // The density sums of a set of one level are added up tile by tile too, so
