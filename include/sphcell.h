@@ -201,7 +201,8 @@ sph_status sph_tree_set_workspace(sph_ctx* ctx, sph_tree* t, void* ws, size_t ws
 /* Bytes a workspace must offer: after a call failed with SPH_E_WORKSPACE, at
  * least what it needed (the blocks in use plus the request, with an eighth of
  * the old size to spare; offer it and repeat the build); otherwise the peak
- * the tree's buffers have used in the current workspace. */
+ * the tree's buffers have used in the current workspace (with the blocks that
+ * it would do without: the order of the chunks, slots of parked walks). */
 sph_status sph_tree_workspace_needed(const sph_tree* t, size_t* bytes);
 
 /* Section II-B (spatial decomposition): for every set, a top grid of cells of

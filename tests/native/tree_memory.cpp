@@ -83,7 +83,7 @@ static void optional_blocks_refuse_nothing() {
     std::mt19937 rng(12345);
     auto pick = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
     int refused = 0, dropped = 0;
-    for (int round = 0; round < 2000; ++round) {
+    for (int trial = 0; trial < 2000; ++trial) {
         sph_tree with, without;
         const size_t bytes = (size_t)pick(1 << 20, (int)room);
         expect(!with.set_workspace(a, bytes, 0).st && !without.set_workspace(b, bytes, 0).st, "attach");
